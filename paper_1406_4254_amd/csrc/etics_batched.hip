@@ -111,7 +111,7 @@ BatchedLayout batched_layout(int64_t ntotal, int nsys, int nmax, int lmax, int p
   L.off_ustart = take(size_t(nsys + 1) * 4);
   L.off_usys = take(size_t(mu) * 4);
   L.off_partials = take(size_t(mu) * 2 * K * 8);
-  L.off_prep = take(size_t(nsys) * 4 * K * (prec == ETICS_FP64 ? 8 : 4));
+  L.off_prep = take(size_t(nsys) * force_prep_bytes(nmax, lmax, prec));
   L.off_A = take(size_t(nsys) * K * 8);
   L.off_B = take(size_t(nsys) * K * 8);
   L.off_acc = take(3 * nn * 8);

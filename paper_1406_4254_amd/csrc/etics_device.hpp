@@ -90,6 +90,38 @@ __device__ __forceinline__ Dual<S> rsqrt_(Dual<S> a) {
   return {q, S(-0.5) * a.d * q * q * q};
 }
 
+
+// Sums of two products, a product taken from a value and a step of a three-term
+// recurrence, with the product that the FMA takes written out: left to the compiler, the
+// choice differs with the code around it and changes the last bit from one kernel to
+// another.
+//   add_prod: a b + c d, FMA on a b;  sub_prod: a b - c d, FMA on a b;  take_prod: s - a b;
+//   recur: x p1 - q p2 (q a constant)
+template <typename S>
+__device__ __forceinline__ S add_prod(S a, S b, S c, S d) { return fma_(a, b, c * d); }
+template <typename S>
+__device__ __forceinline__ S sub_prod(S a, S b, S c, S d) { return fma_(a, b, -(c * d)); }
+template <typename S>
+__device__ __forceinline__ S take_prod(S s, S a, S b) { return fma_(-a, b, s); }
+template <typename S>
+__device__ __forceinline__ S recur(S x, S p1, S q, S p2) { return fma_(x, p1, -(q * p2)); }
+template <typename S>
+__device__ __forceinline__ Dual<S> add_prod(Dual<S> a, Dual<S> b, Dual<S> c, Dual<S> d) {
+  return {fma_(a.v, b.v, c.v * d.v), (a * b).d + (c * d).d};
+}
+template <typename S>
+__device__ __forceinline__ Dual<S> sub_prod(Dual<S> a, Dual<S> b, Dual<S> c, Dual<S> d) {
+  return {fma_(a.v, b.v, -(c.v * d.v)), (a * b).d - (c * d).d};
+}
+template <typename S>
+__device__ __forceinline__ Dual<S> take_prod(Dual<S> s, Dual<S> a, Dual<S> b) {
+  return {fma_(-a.v, b.v, s.v), s.d - (a * b).d};
+}
+template <typename S>
+__device__ __forceinline__ Dual<S> recur(Dual<S> x, Dual<S> p1, S q, Dual<S> p2) {
+  return {fma_(x.v, p1.v, -(q * p2.v)), fma_(-q, p2.d, (x * p1).d)};
+}
+
 template <typename T>
 struct ScalarOf {
   using type = T;
@@ -112,7 +144,7 @@ struct Sph {
 template <typename V, int BASIS = kBasisHO>
 __device__ __forceinline__ Sph<V> sph_v(V x, V y, V z) {
   Sph<V> s;
-  V R2 = x * x + y * y;
+  V R2 = add_prod(x, x, y, y);
   V r2 = R2 + z * z;
   V R = sqrt_(R2);
   s.r = sqrt_(r2);

@@ -1,16 +1,12 @@
 // etics_force.hip -- SCF potential and acceleration on gfx950 (MI355X).
 //
 // The second part of an SCF force calculation (paper Section 3.3): every particle's
-// potential and acceleration from the coefficients A, B.  One particle per lane.
-// For each l the two radial recurrences (Gegenbauer in monic form, for the
-// potential and for d/dr) run over n while the coefficients, the same for every
-// lane, stream through the scalar cache into SGPR operands of the FMAs; the l and m
-// loops are compile-time, so the recurrence and derivative constants are instruction
-// literals.  The angular synthesis uses division-free identities for dYbar/dtheta
-// and m Ybar/sin(theta), and the result is rotated to Cartesian components.  In the
-// batched leapfrog the epilogue applies the kicks (and drift) to the particle instead
-// of storing its acceleration.  No MFMA: the work is basis evaluation and short
-// reductions with ragged shapes.
+// potential and acceleration from the coefficients A, B.  One particle per lane; the
+// synthesis (radial recurrences and sums, angular synthesis, rotation to Cartesian
+// components) is in etics_force_synth.hpp.  FP32 runs the radial sums on the matrix
+// cores, FP64 as FMAs on coefficients broadcast from LDS.  In the batched leapfrog the
+// epilogue applies the kicks (and drift) to the particle instead of storing its
+// acceleration.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -23,18 +19,36 @@
 namespace etics {
 
 // ------------------------------------------------------------------ force prep
-// Coefficients rescaled for the force kernel, four arrays of K in compute precision:
-//   [0,K)   -sqrt(4pi) k_n A          (potential / radial part, with monic C_n)
-//   [K,2K)  -sqrt(4pi) k_n B
-//   [2K,3K) -sqrt(4pi) 2 a_l c k'_{n-1} A  (d/dr part: dC_n^(a)/dxi = 2a C_{n-1}^(a+1))
-//   [3K,4K) -sqrt(4pi) 2 a_l c k'_{n-1} B
+// Coefficients rescaled for the force kernel, in compute precision:
+//   U, V: -sqrt(4pi) k_n (A, B)            (potential / radial part, with monic C_n)
+//   W, X: -sqrt(4pi) 2 a_l c k'_{n-1} (A, B)  (d/dr part: dC_n^(a)/dxi = 2a C_{n-1}^(a+1))
 // where dxi/dr = c g(r): Hernquist-Ostriker c = 2, g = u^2; Clutton-Brock c = 4,
 // g = t u^3 (g is applied per particle by the force kernel).
-template <typename T>
+// The scale of every (basis, n, l) is a constant (as loops of FP64 divisions in the kernel
+// they were most of its 5 to 6 us).
+struct ForceScales {
+  double su[2][NCAP + 1][LCAP + 1], sw[2][NCAP + 1][LCAP + 1];
+};
+constexpr ForceScales make_force_scales() {
+  ForceScales t{};
+  constexpr double s4 = -2.0 * 0x1.c5bf891b4ef6ap+0;  // -sqrt(4 pi), rounded as sqrt(kPi)
+  for (int b = 0; b < 2; ++b)
+    for (int n = 0; n <= NCAP; ++n)
+      for (int l = 0; l <= LCAP; ++l) {
+        const double al = basis_alpha(b, l);
+        const double dxi_c = b == kBasisCB ? 4.0 : 2.0;
+        t.su[b][n][l] = s4 * gegen_k(n, al);
+        t.sw[b][n][l] = n >= 1 ? s4 * 2.0 * al * dxi_c * gegen_k(n - 1, al + 1.0) : 0.0;
+      }
+  return t;
+}
+static __constant__ ForceScales g_force_scales = make_force_scales();
+
+// FP64: two arrays of K, [0,K) U, [K,2K) V (RadialF64 derives the d/dr part)
 __global__ __launch_bounds__(256) void scf_force_prep_kernel(const double* __restrict__ A,
                                                             const double* __restrict__ B,
                                                             int nmax, int lmax, int nsys, int basis,
-                                                            T* __restrict__ cf) {
+                                                            double* __restrict__ cf) {
   const int K = (nmax + 1) * (lmax + 1) * (lmax + 2) / 2;
   const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (g >= int64_t(nsys) * K) return;
@@ -45,24 +59,50 @@ __global__ __launch_bounds__(256) void scf_force_prep_kernel(const double* __res
   const int lm = k - n * L2;
   int l = 0;
   while ((l + 1) * (l + 2) / 2 <= lm) ++l;
-  const double al = basis_alpha(basis, l);
-  const double dxi_c = basis == kBasisCB ? 4.0 : 2.0;
-  const double s4 = -2.0 * sqrt(kPi);
-  const double su = s4 * gegen_k(n, al);
-  const double sw = n >= 1 ? s4 * 2.0 * al * dxi_c * gegen_k(n - 1, al + 1.0) : 0.0;
+  const double su = g_force_scales.su[basis][n][l];
   const double a = A[g], b = B[g];
-  T* c = cf + size_t(sys) * 4 * K;
-  c[k] = T(su * a);
-  c[K + k] = T(su * b);
-  c[2 * K + k] = T(sw * a);
-  c[3 * K + k] = T(sw * b);
+  double* c = cf + size_t(sys) * 2 * K;
+  c[k] = su * a;
+  c[K + k] = su * b;
+}
+
+// FP32: the quad layout of RadialMM, one thread per value
+__global__ __launch_bounds__(256) void scf_force_prep_mm_kernel(const double* __restrict__ A,
+                                                               const double* __restrict__ B,
+                                                               int nmax, int lmax, int nsys, int basis,
+                                                               float* __restrict__ cf) {
+  const int Q = mm_offset(lmax + 1, nmax);
+  const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (g >= int64_t(nsys) * Q) return;
+  const int sys = int(g / Q);
+  int e = int(g - int64_t(sys) * Q);
+  const int rep = 1 + 4 * mm_pairs(nmax);  // runs of padded slots per l
+  int l = 0;
+  while (e >= slot_pad(l, 4) * rep) {
+    e -= slot_pad(l, 4) * rep;
+    ++l;
+  }
+  const int P = slot_pad(l, 4);
+  const int run = e / P, slot = e - run * P;
+  // run 0: order 0 of U, V; then per pair j: U, V of 1+2j, of 2+2j, W, X of 1+2j, of 2+2j
+  const int n = run == 0 ? 0 : 1 + 2 * ((run - 1) / 4) + ((run - 1) & 1);
+  const bool deriv = run > 0 && (((run - 1) >> 1) & 1);
+  float v = 0.f;
+  if (n <= nmax && slot <= 2 * l) {
+    const int m = slot <= l ? slot : slot - l;
+    const int K = (nmax + 1) * (lmax + 1) * (lmax + 2) / 2;
+    const int64_t k = int64_t(sys) * K + n * ((lmax + 1) * (lmax + 2) / 2) + l * (l + 1) / 2 + m;
+    const double scale = deriv ? g_force_scales.sw[basis][n][l] : g_force_scales.su[basis][n][l];
+    v = float(scale * (slot <= l ? A[k] : B[k]));
+  }
+  cf[g] = v;
 }
 
 // ------------------------------------------------------------------------ force
 struct ForceArgs {
   const double *x, *y, *z;
   int64_t n;
-  const void* cf;  // 4K prepared coefficients (T)
+  const void* cf;  // prepared coefficients: quad layout (FP32) or 4K (FP64)
   double *pot, *ax, *ay, *az;
   int K, nmax, lmax;
   int want_pot;
@@ -100,54 +140,91 @@ __device__ __forceinline__ void force_store(const ForceArgs& a, int64_t i, T pot
   }
 }
 
-// potential / acceleration of point i from one system's prepared coefficients cf
-template <typename T, int LB, bool ACC, int BASIS = kBasisHO>
-__device__ __forceinline__ void force_point(const ForceArgs& a, const T* __restrict__ cf,
-                                            int64_t i) {
-  const Sph<T> s = sph<T, BASIS>(a.x[i], a.y[i], a.z[i]);
-  const ForceOut<T> o = synth_point<T, LB, ACC, BASIS>(s, ConstPtr<T>(cf), a.K, a.nmax, a.lmax);
-  force_store<T, ACC>(a, i, o.pot, o.gx, o.gy, o.gz);
+// FP32: potential / acceleration of the points [i0, i1), one per lane, from one system's
+// prepared coefficients.  The matrix cores need every lane of a wavefront, so the loop
+// is uniform over the workgroup and a lane past the end computes a point at the origin.
+// NEXT: the coordinates of a lane's next point are loaded with what the leapfrog update
+// of the current one needs, after the synthesis (one wait instead of two; at lmax > 6
+// the registers for it are not there: 93 -> 143 us at N = 10^6, (10, 10)).
+template <int LB, bool ACC, int BASIS, bool NEXT>
+__device__ __forceinline__ void force_points_mm(const ForceArgs& a, const float* cf, int64_t i0, int64_t i1,
+                                                int64_t stride) {
+  RadialMM<ACC, BASIS> rad(cf, a.nmax, a.lmax);
+  double x = 0.0, y = 0.0, z = 0.0;
+  auto load = [&](int64_t i) {
+    const bool valid = i < i1;
+    x = valid ? a.x[i] : 0.0;
+    y = valid ? a.y[i] : 0.0;
+    z = valid ? a.z[i] : 0.0;
+  };
+  if constexpr (NEXT) load(i0 + threadIdx.x);
+  rad.template start<0>();
+  for (; i0 < i1; i0 += stride) {
+    const int64_t i = i0 + threadIdx.x;
+    if constexpr (!NEXT) load(i);
+    const Sph<float> s = sph<float, BASIS>(x, y, z);
+    const ForceOut<float> o = synth_point<float, LB, ACC, BASIS>(s, rad, a.lmax);
+    if constexpr (NEXT) load(i + stride);
+    // before the stores: loads and stores are waited for in order
+    rad.template start<0>();
+    if (i < i1) force_store<float, ACC>(a, i, o.pot, o.gx, o.gy, o.gz);
+  }
 }
 
 template <typename T, int LB, bool ACC, int BASIS>
-__global__ __launch_bounds__(256) void scf_force_kernel(const ForceArgs a) {
-  const T* __restrict__ cf = reinterpret_cast<const T*>(a.cf);
-  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < a.n;
-       i += int64_t(gridDim.x) * blockDim.x)
-    force_point<T, LB, ACC, BASIS>(a, cf, i);
+__global__ __launch_bounds__(256, LB <= 10 ? 4 : 3) void scf_force_kernel(const ForceArgs a) {
+  static_assert(sizeof(T) == 4, "FP64 runs scf_force_f64_kernel");
+  force_points_mm<LB, ACC, BASIS, false>(a, reinterpret_cast<const float*>(a.cf), int64_t(blockIdx.x) * blockDim.x,
+                                         a.n, int64_t(gridDim.x) * blockDim.x);
 }
 
-// FP64: the workgroup copies the prepared coefficients to LDS once, as [K][4], and every
-// lane reads them as broadcast VGPR operands (as SGPR operands each FP64 coefficient
-// takes two SGPRs and the n loop's set overflows them); a grid of a few workgroups per
-// CU, each walking many points, keeps the copies few.
-template <int LB, bool ACC, int BASIS>
-__global__ __launch_bounds__(256) void scf_force_lds_kernel(const ForceArgs a) {
-  extern __shared__ __align__(16) double lds_cf[];
-  const double* __restrict__ cf = reinterpret_cast<const double*>(a.cf);
-  for (int i = threadIdx.x; i < 4 * a.K; i += blockDim.x) {
-    const int which = i / a.K, idx = i - which * a.K;
-    lds_cf[4 * idx + which] = cf[i];
+// FP64.  One point per lane and no loop over points: in a loop the compiler hoists the
+// FP64 constants (an SGPR pair each) out of it and spills them to vector lanes, 640 lane
+// moves per point at (10, 10).  LDS: the workgroup copies the prepared coefficients to
+// LDS first, as [K][2], and every lane reads them as broadcast VGPR operands.  Such reads
+// are what bounds the pass (a 16-byte broadcast takes the LDS 8 cycles for 64 lanes,
+// whatever it feeds): two doubles per coefficient instead of four, each feeding two FMAs,
+// took N = 10^6, (10, 10) from 261 to 197 us a call and N = 5 10^5, (20, 14) from 783 to
+// 333 us.  Otherwise (potential only, where a read feeds one FMA per double) the
+// coefficients are scalar operands: 119 -> 96 us at N = 10^6, (10, 10).
+template <bool ACC, int BASIS, int LB, typename Radial>
+__device__ __forceinline__ void force_point_f64(const ForceArgs& a, Radial rad, int64_t i) {
+  const Sph<double> s = sph<double, BASIS>(a.x[i], a.y[i], a.z[i]);
+  const ForceOut<double> o = synth_point<double, LB, ACC, BASIS>(s, rad, a.lmax);
+  force_store<double, ACC>(a, i, o.pot, o.gx, o.gy, o.gz);
+}
+// cf [2][K] to the workgroup's LDS [K][2]
+__device__ __forceinline__ void coeffs_to_lds(const double* cf, int K, double* lds) {
+  for (int k = threadIdx.x; k < 2 * K; k += blockDim.x) {
+    const int which = k >= K;
+    lds[2 * (k - which * K) + which] = cf[k];
   }
   __syncthreads();
-  const LdsPtr<double> src = (LdsPtr<double>)(lds_cf);
-  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < a.n;
-       i += int64_t(gridDim.x) * blockDim.x) {
-    const Sph<double> s = sph<double, BASIS>(a.x[i], a.y[i], a.z[i]);
-    const ForceOut<double> o =
-        synth_point<double, LB, ACC, BASIS, LdsPtr<double>, true>(s, src, a.K, a.nmax, a.lmax);
-    force_store<double, ACC>(a, i, o.pot, o.gx, o.gy, o.gz);
+}
+template <int LB, bool ACC, int BASIS, bool LDS>
+__global__ __launch_bounds__(256, 2) void scf_force_f64_kernel(const ForceArgs a) {
+  extern __shared__ __align__(16) double lds_cf[];
+  const double* cf = reinterpret_cast<const double*>(a.cf);
+  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if constexpr (LDS) {
+    coeffs_to_lds(cf, a.K, lds_cf);
+    if (i >= a.n) return;
+    force_point_f64<ACC, BASIS, LB>(
+        a, RadialF64<ACC, BASIS, LdsPtr<double>, true>{(LdsPtr<double>)(lds_cf), a.K, a.nmax, a.lmax}, i);
+  } else {
+    if (i >= a.n) return;
+    force_point_f64<ACC, BASIS, LB>(
+        a, RadialF64<ACC, BASIS, ConstPtr<double>, false>{(ConstPtr<double>)(cf), a.K, a.nmax, a.lmax}, i);
   }
 }
 
 // batched systems: `split` workgroups per unit of `unit` particles of one system (each a
-// contiguous part of it), so the coefficient pointer (and with it every coefficient
-// operand) is uniform across the workgroup; splitting the coefficient kernel's units
-// gives the force pass more workgroups.  The system's prepared coefficients are copied
-// to LDS as [K][4] first, as in scf_force_lds_kernel, and read as broadcast VGPR
-// operands (measured faster than SGPR operands here in FP32 too).
+// contiguous part of it), so the coefficients are uniform across the workgroup; splitting
+// the coefficient kernel's units gives the force pass more workgroups.  FP64: the
+// system's prepared coefficients are copied to LDS as [K][2] first, as in
+// scf_force_f64_kernel; FP32: as in scf_force_kernel.
 template <typename T, int LB, bool ACC>
-__global__ __launch_bounds__(256) void scf_force_batched_kernel(const ForceArgs a,
+__global__ __launch_bounds__(256, sizeof(T) == 8 ? (LB <= 6 ? 3 : 2) : LB <= 10 ? 4 : 3) void scf_force_batched_kernel(const ForceArgs a,
                                                                 const int64_t* __restrict__ offsets,
                                                                 const int* __restrict__ ustart,
                                                                 const int* __restrict__ usys,
@@ -165,23 +242,20 @@ __global__ __launch_bounds__(256) void scf_force_batched_kernel(const ForceArgs 
   const int64_t ue0 = u0 + unit < e ? u0 + unit : e;
   const int64_t ub = u0 + part * kPart < ue0 ? u0 + part * kPart : ue0;
   const int64_t ue = ub + kPart < ue0 ? ub + kPart : ue0;
-  const T* __restrict__ cf = reinterpret_cast<const T*>(a.cf) + size_t(sys) * 4 * a.K;
-  T* lds_t = reinterpret_cast<T*>(lds_cf);
-  for (int i = threadIdx.x; i < 4 * a.K; i += blockDim.x) {
-    const int which = i / a.K, idx = i - which * a.K;
-    lds_t[4 * idx + which] = cf[i];
-  }
-  __syncthreads();
-  const LdsPtr<T> src = (LdsPtr<T>)(lds_t);
-  for (int64_t i = ub + threadIdx.x; i < ue; i += blockDim.x) {
-    const Sph<T> s = sph<T, kBasisHO>(a.x[i], a.y[i], a.z[i]);
-    const ForceOut<T> o = synth_point<T, LB, ACC, kBasisHO, LdsPtr<T>, true>(s, src, a.K, a.nmax, a.lmax);
-    force_store<T, ACC>(a, i, o.pot, o.gx, o.gy, o.gz);
+  if (ub >= ue) return;
+  if constexpr (sizeof(T) == 4) {
+    const float* cf = reinterpret_cast<const float*>(a.cf) +
+                      size_t(__builtin_amdgcn_readfirstlane(sys)) * mm_offset(a.lmax + 1, a.nmax);
+    force_points_mm<LB, ACC, kBasisHO, LB <= 6>(a, cf, ub, ue, blockDim.x);
+  } else {
+    coeffs_to_lds(reinterpret_cast<const double*>(a.cf) + size_t(sys) * 2 * a.K, a.K, lds_cf);
+    const RadialF64<ACC, kBasisHO, LdsPtr<double>, true> rad{(LdsPtr<double>)(lds_cf), a.K, a.nmax, a.lmax};
+    for (int64_t i = ub + threadIdx.x; i < ue; i += blockDim.x) force_point_f64<ACC, kBasisHO, LB>(a, rad, i);
   }
 }
 
 size_t force_prep_bytes(int nmax, int lmax, int prec) {
-  return size_t(4) * coeff_count(nmax, lmax) * (prec == ETICS_FP64 ? 8 : 4);
+  return prec == ETICS_FP64 ? size_t(2) * coeff_count(nmax, lmax) * 8 : size_t(mm_offset(lmax + 1, nmax)) * 4;
 }
 
 namespace {
@@ -200,25 +274,54 @@ void set_lds_limit(const void* kfn) {
   (void)hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
 }
 
+// FP64, one point per lane.  Potential only: scalar coefficient operands for many points
+// and lmax > 6, where the LDS reads bound the pass; elsewhere the scalar loads' latency
+// shows.  LDS against scalar operands, us a call: (10, 10) 26 / 33 at 10^5 points, 43 / 45
+// at 2 10^5, 60 / 59 at 4 10^5, 118 / 102 at 10^6; (10, 6) 25 / 30 at 4 10^5.
+constexpr int64_t kScalarPoints = 400000;
+template <bool ACC, int LBV, int BASIS>
+void launch_force_f64(const ForceArgs& a, hipStream_t st) {
+  const size_t lds = size_t(2) * a.K * sizeof(double);
+  const bool scalar = !ACC && LBV > 6 && a.n >= kScalarPoints;
+  if (!scalar) set_lds_limit(reinterpret_cast<const void*>(scf_force_f64_kernel<LBV, ACC, BASIS, true>));
+  // a grid holds less than 2^32 threads
+  constexpr int64_t kMost = int64_t(1) << 30;
+  for (int64_t at = 0; at < a.n; at += kMost) {
+    ForceArgs b = a;
+    b.n = a.n - at < kMost ? a.n - at : kMost;
+    b.x += at;
+    b.y += at;
+    b.z += at;
+    if (at > 0) {
+      if (b.pot) b.pot += at;
+      if (b.ax) b.ax += at;
+      if (b.ay) b.ay += at;
+      if (b.az) b.az += at;
+    }
+    const dim3 grid(unsigned((b.n + 255) / 256));
+    if constexpr (!ACC && LBV > 6) {
+      if (scalar) {
+        hipLaunchKernelGGL((scf_force_f64_kernel<LBV, ACC, BASIS, false>), grid, dim3(256), 0, st, b);
+        continue;
+      }
+    }
+    hipLaunchKernelGGL((scf_force_f64_kernel<LBV, ACC, BASIS, true>), grid, dim3(256), lds, st, b);
+  }
+}
+
 template <typename T, bool ACC, int LBV>
 void launch_force_kernel(const ForceArgs& a, int basis, int grid, const BatchInfo* bi,
                          hipStream_t st) {
   if (bi) {
-    const size_t lds = size_t(4) * a.K * sizeof(T);
+    const size_t lds = sizeof(T) == 8 ? size_t(2) * a.K * sizeof(T) : 0;
     if (lds) set_lds_limit(reinterpret_cast<const void*>(scf_force_batched_kernel<T, LBV, ACC>));
     hipLaunchKernelGGL((scf_force_batched_kernel<T, LBV, ACC>), dim3(grid), dim3(256), lds, st, a,
                        bi->offsets, bi->ustart, bi->usys, bi->nsys, bi->unit, bi->split);
   } else if constexpr (sizeof(T) == 8) {
-    // a few workgroups per CU, each with the coefficients in LDS
-    const size_t lds = size_t(4) * a.K * sizeof(double);
-    const int g = grid < 1024 ? grid : 1024;
-    if (basis == kBasisCB) {
-      set_lds_limit(reinterpret_cast<const void*>(scf_force_lds_kernel<LBV, ACC, kBasisCB>));
-      hipLaunchKernelGGL((scf_force_lds_kernel<LBV, ACC, kBasisCB>), dim3(g), dim3(256), lds, st, a);
-    } else {
-      set_lds_limit(reinterpret_cast<const void*>(scf_force_lds_kernel<LBV, ACC, kBasisHO>));
-      hipLaunchKernelGGL((scf_force_lds_kernel<LBV, ACC, kBasisHO>), dim3(g), dim3(256), lds, st, a);
-    }
+    if (basis == kBasisCB)
+      launch_force_f64<ACC, LBV, kBasisCB>(a, st);
+    else
+      launch_force_f64<ACC, LBV, kBasisHO>(a, st);
   } else if (basis == kBasisCB)
     hipLaunchKernelGGL((scf_force_kernel<T, LBV, ACC, kBasisCB>), dim3(grid), dim3(256), 0, st, a);
   else
@@ -245,14 +348,14 @@ int launch_force_lb(int lb, const ForceArgs& a, int basis, int grid, const Batch
 
 int launch_prep(const double* A, const double* B, int nmax, int lmax, int nsys, int prec, int basis,
                 void* ws, hipStream_t st) {
-  const int K = coeff_count(nmax, lmax);
-  const int pb = int((int64_t(nsys) * K + 255) / 256);
+  const int64_t values = int64_t(nsys) * (prec == ETICS_FP64 ? coeff_count(nmax, lmax) : mm_offset(lmax + 1, nmax));
+  const int pb = int((values + 255) / 256);
   if (prec == ETICS_FP64)
-    hipLaunchKernelGGL(scf_force_prep_kernel<double>, dim3(pb), dim3(256), 0, st, A, B, nmax, lmax,
-                       nsys, basis, reinterpret_cast<double*>(ws));
+    hipLaunchKernelGGL(scf_force_prep_kernel, dim3(pb), dim3(256), 0, st, A, B, nmax, lmax, nsys, basis,
+                       reinterpret_cast<double*>(ws));
   else
-    hipLaunchKernelGGL(scf_force_prep_kernel<float>, dim3(pb), dim3(256), 0, st, A, B, nmax, lmax,
-                       nsys, basis, reinterpret_cast<float*>(ws));
+    hipLaunchKernelGGL(scf_force_prep_mm_kernel, dim3(pb), dim3(256), 0, st, A, B, nmax, lmax, nsys, basis,
+                       reinterpret_cast<float*>(ws));
   return hip_fail(hipGetLastError(), "scf_force_prep_kernel launch");
 }
 

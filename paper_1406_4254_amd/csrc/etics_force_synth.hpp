@@ -3,12 +3,14 @@
 // (etics_force.hip) and the jerk kernels (etics_jerk.hip).
 //
 // For each l the two radial recurrences (Gegenbauer in monic form, for the potential
-// and for d/dr) run over n while the coefficients, the same for every lane, stream
-// through the scalar cache into SGPR operands of the FMAs; the l and m loops are
-// compile-time, so the recurrence and derivative constants are instruction literals.
-// The angular synthesis uses division-free identities for dYbar/dtheta and
-// m Ybar/sin(theta), and the result is rotated to Cartesian components.  The compute
-// type may carry time derivatives (Dual), which turns the same code into the jerk.
+// and for d/dr) run over n, and the sums over n of recurrence value times coefficient
+// (the same coefficient for every point) come from one of two sources: the matrix cores
+// (RadialMM, FP32) or FMAs on coefficients read as uniform operands (RadialVec, FP64 and
+// Dual).  The l and m loops are compile-time, so the recurrence and derivative constants
+// are instruction literals.  The angular synthesis uses division-free identities for
+// dYbar/dtheta and m Ybar/sin(theta), and the result is rotated to Cartesian components.
+// The compute type may carry time derivatives (Dual), which turns the same code into the
+// jerk.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -63,16 +65,275 @@ struct ForceOut {
   T pot, gx, gy, gz;
 };
 
-// cf: the coefficients' four arrays, through the constant address space (ConstPtr) or
+// Radial sums of one l over n, for every m: U, V (potential; cos and sin coefficients)
+// from Chat_n and W, X (d/dr) from Ehat_{n-1} (parameter a_l + 1).  Order 0 is taken in
+// closed form (Chat_0 = 1; it adds nothing to W, X since Ehat_{-1} = 0).
+//
+// RadialVec: one FMA per coefficient.  The coefficients' four arrays are read through
+// the constant address space (ConstPtr; wave-uniform scalar loads into SGPR operands) or
 // in LDS (LdsPtr); laid out [4][K], or with QUAD [K][4] (the four values of a
-// coefficient side by side, two 16-byte reads in FP64)
-template <typename T, int LB, bool ACC, int BASIS, typename P = ConstPtr<T>, bool QUAD = false>
-__device__ __forceinline__ ForceOut<T> synth_point(const Sph<T>& s, P cf, int K, int nmax, int lmax) {
-  const int WK = QUAD ? 1 : K;      // offset from one array to the next
-  constexpr int IS = QUAD ? 4 : 1;  // offset from one coefficient to the next
+// coefficient side by side, two 16-byte reads in FP64).
+template <typename T, bool ACC, int BASIS, typename P = ConstPtr<T>, bool QUAD = false>
+struct RadialVec {
+  P cf;
+  int K, nmax, lmax;
+
+  template <int l>
+  __device__ __forceinline__ void start() {}
+
+  template <int l>
+  __device__ __forceinline__ void sums(T xi, T (&U)[l + 1], T (&V)[l + 1], T (&W)[l + 1], T (&X)[l + 1]) {
+    const int WK = QUAD ? 1 : K;      // offset from one array to the next
+    constexpr int IS = QUAD ? 4 : 1;  // offset from one coefficient to the next
+    using S = typename ScalarOf<T>::type;
+    const BasisTables<S>& tb = tab<S>();
+    const int L2 = (lmax + 1) * (lmax + 2) / 2;
+    const P cfl = cf + l * (l + 1) / 2 * IS;
+#pragma unroll
+    for (int m = 0; m <= l; ++m) {
+      U[m] = cload(cfl + m * IS);
+      V[m] = m > 0 ? cload(cfl + WK + m * IS) : T(0);
+      W[m] = T(0);
+      X[m] = T(0);
+    }
+    T c2 = T(0), c1 = T(1);  // Chat_{n-2}, Chat_{n-1} for n = 1 (Chat_{-1} enters times 0)
+    T e2 = T(0), e1 = T(1);  // Ehat_{n-2}, Ehat_{n-1} (parameter a_l + 1)
+    const S* ql = BASIS == kBasisCB ? tb.qcb[l] : tb.q[l];
+    const S* qdl = BASIS == kBasisCB ? tb.qdcb[l] : tb.qd[l];
+    // one order per trip keeps the coefficients of a trip in registers
+    for (int nn = 1; nn <= nmax; ++nn) {
+      const T c = recur(xi, c1, ql[nn], c2);  // Chat_nn
+      const auto* cn = cfl + nn * L2 * IS;
+#pragma unroll
+      for (int m = 0; m <= l; ++m) {
+        U[m] = fma_(c, cload(cn + m * IS), U[m]);
+        if (m > 0) V[m] = fma_(c, cload(cn + WK + m * IS), V[m]);
+      }
+      c2 = c1;
+      c1 = c;
+      if constexpr (ACC) {
+#pragma unroll
+        for (int m = 0; m <= l; ++m) {
+          W[m] = fma_(e1, cload(cn + 2 * WK + m * IS), W[m]);
+          if (m > 0) X[m] = fma_(e1, cload(cn + 3 * WK + m * IS), X[m]);
+        }
+        const T e = recur(xi, e1, qdl[nn], e2);  // Ehat_nn
+        e2 = e1;
+        e1 = e;
+      }
+    }
+  }
+};
+
+// RadialF64: plain FP64.  The d/dr family needs no coefficients of its own: with monic
+// polynomials d Chat_n / d xi = n Ehat_{n-1}, so W, X take n c Ehat_{n-1} (dxi/dr = c g)
+// times the coefficients of U, V, and every coefficient read feeds two FMAs.
+template <bool ACC, int BASIS, typename P, bool PAIR>
+struct RadialF64 {
+  P cf;  // [2][K], or with PAIR [K][2]
+  int K, nmax, lmax;
+
+  template <int l>
+  __device__ __forceinline__ void start() {}
+
+  template <int l>
+  __device__ __forceinline__ void sums(double xi, double (&U)[l + 1], double (&V)[l + 1], double (&W)[l + 1],
+                                       double (&X)[l + 1]) {
+    const int VK = PAIR ? 1 : K;
+    constexpr int IS = PAIR ? 2 : 1;
+    const BasisTables<double>& tb = tab<double>();
+    const int L2 = (lmax + 1) * (lmax + 2) / 2;
+    const P cfl = cf + l * (l + 1) / 2 * IS;
+#pragma unroll
+    for (int m = 0; m <= l; ++m) {
+      U[m] = cload(cfl + m * IS);
+      V[m] = m > 0 ? cload(cfl + VK + m * IS) : 0.0;
+      W[m] = 0.0;
+      X[m] = 0.0;
+    }
+    double c2 = 0.0, c1 = 1.0;  // Chat_{n-2}, Chat_{n-1} for n = 1
+    double e2 = 0.0, e1 = 1.0;  // Ehat_{n-2}, Ehat_{n-1}
+    double cn = 0.0;            // c n
+    const double* ql = BASIS == kBasisCB ? tb.qcb[l] : tb.q[l];
+    const double* qdl = BASIS == kBasisCB ? tb.qdcb[l] : tb.qd[l];
+    auto step = [&](int nn, double& cA, double& cB, double& eA, double& eB) {
+      cA = recur(xi, cB, ql[nn], cA);
+      double ec = 0.0;
+      if constexpr (ACC) {
+        cn += BASIS == kBasisCB ? 4.0 : 2.0;
+        ec = cn * eB;
+      }
+      const auto* p = cfl + nn * L2 * IS;
+#pragma unroll
+      for (int m = 0; m <= l; ++m) {
+        const double a = cload(p + m * IS);
+        U[m] = fma_(cA, a, U[m]);
+        if constexpr (ACC) W[m] = fma_(ec, a, W[m]);
+        if (m > 0) {
+          const double b = cload(p + VK + m * IS);
+          V[m] = fma_(cA, b, V[m]);
+          if constexpr (ACC) X[m] = fma_(ec, b, X[m]);
+        }
+      }
+      if constexpr (ACC) eA = recur(xi, eB, qdl[nn], eA);
+    };
+    int nn = 1;
+    for (; nn + 1 <= nmax; nn += 2) {
+      step(nn, c2, c1, e2, e1);
+      step(nn + 1, c1, c2, e1, e2);
+    }
+    if (nn <= nmax) step(nn, c2, c1, e2, e1);
+  }
+};
+
+// RadialMM: the sums on the matrix cores (FP32).  v_mfma_f32_4x4x1 multiplies, in each
+// of 16 blocks, 4 A values (lanes 4b .. 4b+3) with 4 B values (the same lanes) into a
+// 4 x 4 accumulator whose column j is the four registers of lane 4b+j.  With A = the
+// coefficients of 4 (cos or sin) slots and B = the lane's own recurrence value, a lane
+// so accumulates 4 slots of its own point: no lane moves, and each accumulator goes
+// through the same chain of FMAs (one rounding each) as four vector FMAs would.  The
+// instruction can take A from one of its 16 blocks (CBSZ = 4, ABID = block), so one
+// register holds the coefficients of 16 such quads of slots, loaded once by 64 lanes.
+// Every lane of the wavefront takes part (the matrix cores ignore EXEC): callers keep
+// the wavefront together and give lanes without a point any finite coordinates.
+//
+// Prepared layout of one l, with nq = quads of its 2l+1 slots (U_0..U_l, V_1..V_l,
+// padded with zeros): order 0 of U, V [nq][4]; then per pair of orders n = 1+2j, 2+2j
+// the U, V coefficients [2][nq][4] and the W, X coefficients [2][nq][4] (zero past
+// nmax).  The l's follow each other.
+//
+// What bounds it: VALU issue.  As vector FMAs the sums were 2420 of the 4460 VALU
+// instructions per wavefront at (10, 10), issued in 83% of the cycles; a quad is one
+// instruction in their place, and its 8 matrix-core cycles pass beside other wavefronts'
+// recurrences and angular sums.  N = 10^6, (10, 10), potential and acceleration: 135 ->
+// 93 us a call; potential only 68 -> 46 us; N = 2 10^6, (20, 14): 873 -> 472 us; N = 10^4,
+// (10, 6): 25 -> 16 us.  Coefficient loads through 64-bit vector addresses kept one
+// address pair per l in registers (181 VGPRs, two wavefronts per SIMD: 109 us), and
+// recurrence constants through scalar loads left a wait in every pair (100 us).
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+template <int BLOCK>
+__device__ __forceinline__ f32x4_t mfma_quad(float a, float b, f32x4_t c) {
+  return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, BLOCK, 0);
+}
+__host__ __device__ constexpr int mm_quads(int l) { return slot_pad(l, 4) / 4; }
+// pairs of orders from order 1 on (at least one, so the first needs no branch)
+__host__ __device__ constexpr int mm_pairs(int nmax) { return nmax < 1 ? 1 : (nmax + 1) / 2; }
+// floats of the l's before l, and of the whole array (l = lmax + 1)
+__host__ __device__ constexpr int mm_offset(int l, int nmax) { return zoff(l, 4) * (1 + 4 * mm_pairs(nmax)); }
+
+template <bool ACC, int BASIS>
+struct RadialMM {
+  // The coefficients through a buffer descriptor: its base and the position are scalar,
+  // so a lane keeps one offset register for every load, and the lanes past the values of
+  // a short run read the following ones, or zero past the array's end.
+  __amdgpu_buffer_rsrc_t cf;
+  int nmax, lane4;        // lane4: the lane's byte offset
+  int pos;                // start of the current l
+  // this lane's coefficients: order 0; the next two pairs of orders (U, V and W, X)
+  float a0, x0, y0, x1, y1;
+
+  // cfp: the prepared coefficients of one system, the same pointer in every lane
+  __device__ __forceinline__ RadialMM(const float* cfp, int nmax_, int lmax_)
+      : cf(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(cfp), 0, 4 * mm_offset(lmax_ + 1, nmax_),
+                                             0x00020000)),
+        nmax(nmax_), lane4(4 * int(threadIdx.x & 63)), pos(0), a0(0.f), x0(0.f), y0(0.f), x1(0.f), y1(0.f) {}
+
+  // this lane's float at position pos + off
+  __device__ __forceinline__ float load(int off) const {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(cf, lane4, 4 * (pos + off), 0));
+  }
+  // one register holds a pair's U, V and W, X quads if they are at most 16
+  template <int l>
+  static constexpr bool one_reg() { return ACC && 4 * mm_quads(l) <= 16; }
+
+  // pair J of the orders of l (past the last pair: other values, not used)
+  template <int l, int J>
+  __device__ __forceinline__ void load_pair(float& x, float& y) const {
+    constexpr int at = 4 * mm_quads(l) * (1 + 4 * J);
+    x = load(at);
+    if constexpr (ACC && !one_reg<l>()) y = load(at + 8 * mm_quads(l));
+  }
+  // the first loads of l, issued before the previous l's angular synthesis
+  template <int l>
+  __device__ __forceinline__ void start() {
+    if constexpr (l == 0) pos = 0;
+    a0 = load(0);
+    load_pair<l, 0>(x0, y0);
+    load_pair<l, 1>(x1, y1);
+  }
+
+  template <int l>
+  __device__ __forceinline__ void sums(float xi, float (&U)[l + 1], float (&V)[l + 1], float (&W)[l + 1],
+                                       float (&X)[l + 1]) {
+    constexpr int NQ = mm_quads(l);
+    const f32x4_t zero{0.f, 0.f, 0.f, 0.f};
+    f32x4_t uv[NQ], wx[NQ];
+    static_for<NQ>([&](auto qc) {
+      constexpr int q = decltype(qc)::value;
+      uv[q] = mfma_quad<q>(a0, 1.0f, zero);
+    });
+    float c2 = 0.f, c1 = 1.f;  // Chat_{n-2}, Chat_{n-1} for n = 1
+    float e2 = 0.f, e1 = 1.f;  // Ehat_{n-2}, Ehat_{n-1}
+    // order NN: c <- Chat_NN, accumulate, advance Ehat
+    auto step = [&](auto nc, float x, float y, float& cA, float& cB, float& eA, float& eB) {
+      constexpr int NN = decltype(nc)::value;
+      constexpr int PAR = (NN - 1) % 2;
+      constexpr float q = float(BASIS == kBasisCB ? kTab.qcb[l][NN] : kTab.q[l][NN]);
+      constexpr float qd = float(BASIS == kBasisCB ? kTab.qdcb[l][NN] : kTab.qd[l][NN]);
+      cA = recur(xi, cB, q, cA);
+      static_for<NQ>([&](auto qc) {
+        constexpr int b = decltype(qc)::value;
+        uv[b] = mfma_quad<PAR * NQ + b>(x, cA, uv[b]);
+      });
+      if constexpr (ACC) {
+        static_for<NQ>([&](auto qc) {
+          constexpr int b = decltype(qc)::value;
+          const f32x4_t w = NN == 1 ? zero : wx[b];
+          if constexpr (one_reg<l>())
+            wx[b] = mfma_quad<(2 + PAR) * NQ + b>(x, eB, w);
+          else
+            wx[b] = mfma_quad<PAR * NQ + b>(y, eB, w);
+        });
+        eA = recur(xi, eB, qd, eA);
+      }
+    };
+    // The pairs are unrolled up to the cap, so the recurrence constants are literals and
+    // the positions immediate offsets, with a uniform exit after each.  Every pair runs
+    // both orders: past nmax (odd cutoffs) the coefficients are zero, cheaper than a
+    // branch.  Two register sets take turns; a set is loaded for two pairs on as soon as
+    // its pair is issued, without a condition (what lies past the last pair is not used).
+    int npairs = mm_pairs(nmax);
+    // opaque, so that the exit tests are compares here and not 64-bit masks kept (and
+    // spilled to vector lanes) over the loop on points
+    asm volatile("" : "+s"(npairs));
+    auto pairs = [&](auto self, auto jc) -> void {
+      constexpr int J = decltype(jc)::value;
+      float& x = J % 2 ? x1 : x0;
+      float& y = J % 2 ? y1 : y0;
+      step(std::integral_constant<int, 1 + 2 * J>{}, x, y, c2, c1, e2, e1);
+      step(std::integral_constant<int, 2 + 2 * J>{}, x, y, c1, c2, e1, e2);
+      if constexpr (J + 2 < mm_pairs(NCAP)) load_pair<l, J + 2>(x, y);
+      if constexpr (J + 1 < mm_pairs(NCAP)) {
+        if (J + 1 < npairs) self(self, std::integral_constant<int, J + 1>{});
+      }
+    };
+    pairs(pairs, std::integral_constant<int, 0>{});
+    pos += 4 * NQ * (1 + 4 * npairs);
+#pragma unroll
+    for (int m = 0; m <= l; ++m) {
+      U[m] = uv[m / 4][m % 4];
+      W[m] = wx[m / 4][m % 4];
+      V[m] = m > 0 ? uv[(l + m) / 4][(l + m) % 4] : 0.f;
+      X[m] = m > 0 ? wx[(l + m) / 4][(l + m) % 4] : 0.f;
+    }
+  }
+};
+
+// Potential and acceleration at a point with spherical coordinates s; rad gives the radial
+// sums (RadialVec or RadialMM, whose start<0>() the caller has called)
+template <typename T, int LB, bool ACC, int BASIS, typename Radial>
+__device__ __forceinline__ ForceOut<T> synth_point(const Sph<T>& s, Radial& rad, int lmax) {
   using S = typename ScalarOf<T>::type;
-  const BasisTables<S>& tb = tab<S>();
-  const int L2 = (lmax + 1) * (lmax + 2) / 2;
   ForceOut<T> out{};
   {
     const T tu = s.t * s.u, u2 = s.u * s.u;
@@ -88,8 +349,8 @@ __device__ __forceinline__ ForceOut<T> synth_point(const Sph<T>& s, P cf, int K,
     sm[0] = T(0);
 #pragma unroll
     for (int m = 1; m <= LB; ++m) {
-      cm[m] = cm[m - 1] * s.cp - sm[m - 1] * s.sp;
-      sm[m] = sm[m - 1] * s.cp + cm[m - 1] * s.sp;
+      cm[m] = sub_prod(cm[m - 1], s.cp, sm[m - 1], s.sp);
+      sm[m] = add_prod(sm[m - 1], s.cp, cm[m - 1], s.sp);
     }
 
     // Legendre rows; row l+1 is needed for m Ybar_lm / sin(theta)
@@ -101,7 +362,7 @@ __device__ __forceinline__ ForceOut<T> synth_point(const Sph<T>& s, P cf, int K,
       Y[r][r - 1] = T(kTab.c1[r][r - 1]) * s.ct * Y[r - 1][r - 1];
       static_for<(r >= 2 ? r - 1 : 0)>([&](auto mc) {
         constexpr int m = decltype(mc)::value;
-        Y[r][m] = (T(kTab.c1[r][m]) * s.ct) * Y[r - 1][m] - T(kTab.c2[r][m]) * Y[r - 2][m];
+        Y[r][m] = sub_prod(T(kTab.c1[r][m]) * s.ct, Y[r - 1][m], T(kTab.c2[r][m]), Y[r - 2][m]);
       });
     };
 
@@ -117,87 +378,40 @@ __device__ __forceinline__ ForceOut<T> synth_point(const Sph<T>& s, P cf, int K,
         legendre_row(std::integral_constant<int, l>{});
       }
 
-      // radial sums over n: U,V (potential), W,X (radial derivative).  Order 0 is taken
-      // in closed form (Chat_0 = 1; it adds nothing to W, X since Ehat_{-1} = 0), the
-      // loop starts at order 1.
-      // the prepared coefficients are read-only here: through the constant address
-      // space their wave-uniform loads become scalar loads into SGPR operands (for FP64
-      // as well, where the generic pointer left the compiler with per-lane loads)
-      const P cfl = cf + l * (l + 1) / 2 * IS;
       T U[l + 1], V[l + 1], W[l + 1], X[l + 1];
-#pragma unroll
-      for (int m = 0; m <= l; ++m) {
-        U[m] = cload(cfl + m * IS);
-        V[m] = m > 0 ? cload(cfl + WK + m * IS) : T(0);
-        W[m] = T(0);
-        X[m] = T(0);
-      }
-      T c2 = T(0), c1 = T(1);  // Chat_{n-2}, Chat_{n-1} for n = 1 (Chat_{-1} enters times 0)
-      T e2 = T(0), e1 = T(1);  // Ehat_{n-2}, Ehat_{n-1} (parameter a_l + 1)
-      const S* ql = BASIS == kBasisCB ? tb.qcb[l] : tb.q[l];
-      const S* qdl = BASIS == kBasisCB ? tb.qdcb[l] : tb.qd[l];
-      // one radial order: c <- Chat_nn, accumulate, advance Ehat
-      auto step = [&](int nn, T& cA, T& cB, T& eA, T& eB) {
-        // on entry cA = Chat_{nn-2}, cB = Chat_{nn-1}; on exit cA = Chat_nn
-        cA = s.xi * cB - ql[nn] * cA;
-        const auto* cn = cfl + nn * L2 * IS;
-#pragma unroll
-        for (int m = 0; m <= l; ++m) {
-          U[m] = fma_(cA, cload(cn + m * IS), U[m]);
-          if (m > 0) V[m] = fma_(cA, cload(cn + WK + m * IS), V[m]);
-        }
-        if constexpr (ACC) {
-          // eB = Ehat_{nn-1} is used, then eA <- Ehat_nn
-#pragma unroll
-          for (int m = 0; m <= l; ++m) {
-            W[m] = fma_(eB, cload(cn + 2 * WK + m * IS), W[m]);
-            if (m > 0) X[m] = fma_(eB, cload(cn + 3 * WK + m * IS), X[m]);
-          }
-          eA = s.xi * eB - qdl[nn] * eA;
-        }
-      };
-      if constexpr (sizeof(T) == 4) {
-        // two orders per trip: the recurrence registers swap roles instead of moving
-        int nn = 1;
-        for (; nn + 1 <= nmax; nn += 2) {
-          step(nn, c2, c1, e2, e1);      // c2 <- Chat_nn, e2 <- Ehat_nn
-          step(nn + 1, c1, c2, e1, e2);  // c1 <- Chat_{nn+1}, e1 <- Ehat_{nn+1}
-        }
-        if (nn <= nmax) step(nn, c2, c1, e2, e1);
-      } else {
-        // FP64 coefficients take two SGPRs each: one order per trip keeps them in SGPRs
-        for (int nn = 1; nn <= nmax; ++nn) {
-          step(nn, c2, c1, e2, e1);
-          const T tc = c2, te = e2;
-          c2 = c1;
-          c1 = tc;
-          e2 = e1;
-          e1 = te;
-        }
+      rad.template sums<l>(s.xi, U, V, W, X);
+      if constexpr (l < LB) {
+        if (l < lmax) rad.template start<l + 1>();
       }
 
       // angular synthesis for this l
       T Pl = T(0), Gl = T(0), Tl = T(0), Fl = T(0);
       static_for<l + 1>([&](auto mc) {
         constexpr int m = decltype(mc)::value;
-        const T ec = U[m] * cm[m] + V[m] * sm[m];
+        const T ec = m >= (ACC ? l - 1 : l) ? add_prod(V[m], sm[m], U[m], cm[m]) : add_prod(U[m], cm[m], V[m], sm[m]);
         Pl = fma_(Y[l][m], ec, Pl);
         if constexpr (ACC) {
-          const T gc = W[m] * cm[m] + X[m] * sm[m];
+          const T gc = add_prod(W[m], cm[m], X[m], sm[m]);
           Gl = fma_(Y[l][m], gc, Gl);
           if constexpr (l >= 1) {
             T dY;
             if constexpr (m == 0) {
               dY = T(kTab.e1[l][0]) * Y[l][1];
             } else if constexpr (m + 1 <= l) {
-              dY = T(kTab.e1[l][m]) * Y[l][m + 1] - T(kTab.e2[l][m]) * Y[l][m - 1];
+              if constexpr (l == 2 && m == 1)  // e1 = 1
+                dY = take_prod(Y[l][m + 1], T(kTab.e2[l][m]), Y[l][m - 1]);
+              else
+                dY = sub_prod(T(kTab.e1[l][m]), Y[l][m + 1], T(kTab.e2[l][m]), Y[l][m - 1]);
             } else {
               dY = -T(kTab.e2[l][m]) * Y[l][m - 1];
             }
             Tl = fma_(dY, ec, Tl);
             if constexpr (m >= 1) {
-              const T fc = V[m] * cm[m] - U[m] * sm[m];
-              const T mYs = -(T(kTab.f1[l][m]) * Y[l + 1][m + 1] + T(kTab.f2[l][m]) * Y[l + 1][m - 1]);
+              const T fc = sub_prod(V[m], cm[m], U[m], sm[m]);
+              const T f1 = T(kTab.f1[l][m]), f2 = T(kTab.f2[l][m]);
+              // (the other product in a plain kernel's last row)
+              const T mYs = l < LB || sizeof(T) != sizeof(S) ? -add_prod(f1, Y[l + 1][m + 1], f2, Y[l + 1][m - 1])
+                                   : -add_prod(f2, Y[l + 1][m - 1], f1, Y[l + 1][m + 1]);
               Fl = fma_(mYs, fc, Fl);
             }
           }
@@ -206,15 +420,18 @@ __device__ __forceinline__ ForceOut<T> synth_point(const Sph<T>& s, P cf, int K,
       accP = fma_(Rl, Pl, accP);
       if constexpr (ACC) {
         const T Ql = Rprev * u2;                             // t^(l-1) u^(l+2) = (t^l u^(l+1))/r
-        const T dRl = T(l) * Ql - T(2 * l + 1) * Rl * hfac;  // d/dr (t^l u^(l+1))
-        T ar = dRl * Pl + Rl * gfac * Gl;
+        // d/dr (t^l u^(l+1))
+        const T dRl = l == 0   ? -(Rl * hfac)
+                      : l == 1 ? take_prod(Ql, T(3) * Rl, hfac)
+                               : sub_prod(T(l), Ql, T(2 * l + 1) * Rl, hfac);
+        T ar = l <= 1 ? add_prod(Rl * gfac, Gl, dRl, Pl) : add_prod(dRl, Pl, Rl * gfac, Gl);
         if constexpr (l == 0) {
           if (!(s.r > T(0))) ar = T(0);  // no direction at the origin
         }
         accR -= ar;
         if constexpr (l >= 1) {
-          accT -= Ql * Tl;
-          accF -= Ql * Fl;
+          accT = take_prod(accT, Ql, Tl);
+          accF = take_prod(accF, Ql, Fl);
         }
       }
       Rprev = Rl;
@@ -222,9 +439,9 @@ __device__ __forceinline__ ForceOut<T> synth_point(const Sph<T>& s, P cf, int K,
     });
     out.pot = accP;
     if constexpr (ACC) {
-      out.gx = s.st * s.cp * accR + s.ct * s.cp * accT - s.sp * accF;
-      out.gy = s.st * s.sp * accR + s.ct * s.sp * accT + s.cp * accF;
-      out.gz = s.ct * accR - s.st * accT;
+      out.gx = take_prod(add_prod(s.st * s.cp, accR, s.ct * s.cp, accT), s.sp, accF);
+      out.gy = add_prod(s.st * s.sp, accR, s.ct * s.sp, accT) + s.cp * accF;
+      out.gz = sub_prod(s.ct, accR, s.st, accT);
     }
   }
   return out;
