@@ -12,11 +12,15 @@
 //
 // Steps (all on the caller's stream):
 //   1. mex_keys: FP64 key (x*x + y*y) + z*z, each operation rounded, as its IEEE bit
-//      pattern (order-preserving for non-negative values), with the particle index.
-//   2. LSD radix sort of (key, index), 8 bits per pass, three kernels per pass: the
-//      digit counts of every tile of keys, a scan of each digit's counts over the tiles,
-//      then every tile ranks its keys stably in LDS and writes them as runs of equal
-//      digit.  Stable, so equal keys stay in index order.
+//      pattern (order-preserving for non-negative values).
+//   2. The order of (key, index).  Up to kRankMost particles: every particle counts the
+//      smaller keys (one kernel, with step 1).  Up to kSampleMost: a sample sort, whose
+//      256 buckets are bounded by sampled (key, index) pairs, so equal keys split too: one
+//      stable pass puts the keys into their buckets, then a workgroup sorts each bucket in
+//      LDS.  Above: LSD radix sort, 8 bits per pass, three kernels per pass: the digit
+//      counts of every tile of keys, a scan of each digit's counts over the tiles, then
+//      every tile ranks its keys stably in LDS and writes them as runs of equal digit.
+//      Every variant leaves equal keys in index order.
 //   3. tile sums: per tile of 128 sorted particles, the sums of the inward and outward
 //      summands (FP64).  FP32-basis modes (mex_tile_sums_pair_kernel): one wavefront per
 //      tile, two particles per lane; the lane pair sums go through the wavefront's own
@@ -56,6 +60,18 @@ constexpr int kSortThreads = 256;
 constexpr int kSortKPT = 8;                         // keys per thread of a radix pass
 constexpr int kSortTile = kSortThreads * kSortKPT;  // keys per tile of a radix pass
 constexpr int kSortPasses = 8;                      // 8-bit digits of a 64-bit key
+constexpr int kBuckets = 256;                       // sample sort: buckets,
+constexpr int kSamples = 16 * kBuckets;             // samples,
+constexpr int kBucketThreads = 1024;                // threads that sort a bucket,
+constexpr int kBucketKPT = 11;                      // keys of each,
+constexpr int kBucketTile = kBucketThreads * kBucketKPT;  // and the keys that LDS holds at once
+// Where the line between the sorts lies, us a MEX call at lmax 10 (radix sort alone / as
+// chosen here): the rank count is O(n^2), but one kernel: 143 / 54 at 1000 particles, 164 /
+// 77 at 8000 (94 at 9000 with the sample sort); sample sort 181 / 111 at 10^5, 490 / 397 at
+// 10^6.  A bucket holds 16 samples' worth of keys; up to kSampleMost one that outgrows the
+// LDS has to be 2.75 times the mean (of random inputs, one in 10^4 has such a bucket).
+constexpr int64_t kRankMost = 8192;
+constexpr int64_t kSampleMost = int64_t(kBuckets) * 4096;
 
 // ------------------------------------------------------------------ block scans
 // exclusive prefix sum of one value per thread over a workgroup of 256 threads
@@ -96,7 +112,91 @@ __global__ __launch_bounds__(256) void mex_keys_kernel(const double* __restrict_
   const double zz = __dmul_rn(z[i], z[i]);
   const double k = __dadd_rn(__dadd_rn(xx, yy), zz);
   key[i] = __double_as_longlong(k);
-  idx[i] = uint32_t(i);
+  if (idx) idx[i] = uint32_t(i);
+}
+
+__device__ __forceinline__ uint64_t mex_key(double x, double y, double z) {
+  return __double_as_longlong(__dadd_rn(__dadd_rn(__dmul_rn(x, x), __dmul_rn(y, y)), __dmul_rn(z, z)));
+}
+
+// ------------------------------------------------------------------ rank by counting
+// perm[rank of i] = i for few particles.  A workgroup holds all keys in LDS and ranks 16
+// particles; its 16 slices of lanes count over every 16th key.  rank = smaller keys plus
+// equal keys of lower index, so every rank occurs once whatever the keys are.
+// Every STEP-th of n keys from `slice` on: how many come before key ki of number i, which is
+// one of nt numbers from i0 (uniform) on.
+template <int STEP>
+__device__ __forceinline__ uint32_t count_before(const uint64_t* key, uint64_t ki, int i, int i0, int nt, int slice,
+                                                 int n) {
+  uint32_t c = 0;
+  int j = slice;
+#pragma unroll 8
+  for (; j < i0; j += STEP) c += key[j] <= ki ? 1u : 0u;
+  for (; j < i0 + nt && j < n; j += STEP) c += key[j] < ki || (key[j] == ki && j < i) ? 1u : 0u;
+#pragma unroll 8
+  for (; j < n; j += STEP) c += key[j] < ki ? 1u : 0u;
+  return c;
+}
+constexpr int kRankThreads = 256, kRankTargets = 16;
+__global__ __launch_bounds__(kRankThreads) void mex_rank_kernel(const double* __restrict__ x,
+                                                                const double* __restrict__ y,
+                                                                const double* __restrict__ z, int n,
+                                                                uint32_t* __restrict__ perm) {
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  uint64_t* key = reinterpret_cast<uint64_t*>(lds_raw);
+  __shared__ uint32_t cnt[kRankThreads / kRankTargets][kRankTargets];
+  for (int j = threadIdx.x; j < n; j += kRankThreads) key[j] = mex_key(x[j], y[j], z[j]);
+  __syncthreads();
+  constexpr int kSlices = kRankThreads / kRankTargets;
+  const int tl = threadIdx.x % kRankTargets, slice = threadIdx.x / kRankTargets;
+  const int i = blockIdx.x * kRankTargets + tl;
+  const uint64_t ki = key[i < n ? i : n - 1];
+  uint32_t c = count_before<kSlices>(key, ki, i, blockIdx.x * kRankTargets, kRankTargets, slice, n);
+  cnt[slice][tl] = c;
+  __syncthreads();
+  if (slice != 0 || i >= n) return;
+  for (int q = 1; q < kSlices; ++q) c += cnt[q][tl];
+  if (c < uint32_t(n)) perm[c] = uint32_t(i);  // always true; keeps a logic error inside the output
+}
+
+// ------------------------------------------------------------------ sample sort
+// (key, index) pairs in order
+__device__ __forceinline__ bool pair_less(uint64_t ka, uint32_t ia, uint64_t kb, uint32_t ib) {
+  return ka < kb || (ka == kb && ia < ib);
+}
+// particle of sample s: one in each of kSamples equal stretches of the input, at a hashed
+// place in it (a fixed stride could follow a period of the input)
+__device__ __forceinline__ uint32_t sample_particle(int s, int64_t n) {
+  const int64_t a = int64_t(s) * n / kSamples, b = int64_t(s + 1) * n / kSamples;
+  uint32_t h = uint32_t(s) * 2654435761u;
+  h ^= h >> 15;
+  return uint32_t(a + int64_t((uint64_t(h) * uint32_t(b - a)) >> 32));
+}
+// Splitters: the samples of rank 16, 32, ... bound the buckets from below; every workgroup
+// ranks 16 of the samples by counting over all of them, as mex_rank_kernel does.
+constexpr int kSplitThreads = 1024;
+__global__ __launch_bounds__(kSplitThreads) void mex_splitters_kernel(const uint64_t* __restrict__ key, int64_t n,
+                                                                     uint64_t* __restrict__ skey,
+                                                                     uint32_t* __restrict__ sidx) {
+  constexpr int kSlices = kSplitThreads / kRankTargets;
+  __shared__ uint64_t k[kSamples];
+  __shared__ uint32_t cnt[kSlices][kRankTargets];
+#pragma unroll
+  for (int s = 0; s < kSamples; s += kSplitThreads)
+    k[s + threadIdx.x] = key[sample_particle(s + threadIdx.x, n)];
+  __syncthreads();
+  // samples of higher number are of higher index: the number breaks ties
+  const int tl = threadIdx.x % kRankTargets, slice = threadIdx.x / kRankTargets;
+  const int i = blockIdx.x * kRankTargets + tl;
+  uint32_t c = count_before<kSlices>(k, k[i], i, blockIdx.x * kRankTargets, kRankTargets, slice, kSamples);
+  cnt[slice][tl] = c;
+  __syncthreads();
+  if (slice != 0) return;
+  for (int q = 1; q < kSlices; ++q) c += cnt[q][tl];
+  if (c % (kSamples / kBuckets) == 0) {
+    skey[c / (kSamples / kBuckets)] = k[i];
+    sidx[c / (kSamples / kBuckets)] = sample_particle(i, n);
+  }
 }
 
 // ------------------------------------------------------------------ radix sort
@@ -142,6 +242,39 @@ __global__ __launch_bounds__(kSortThreads) void radix_count_kernel(const uint64_
   counts[size_t(t) * ntiles + blockIdx.x] = h[t];
 }
 
+// The same for the bucket of every key (digit[i], 0 .. 255): the last splitter, from 1 on,
+// that is not above (key, index), found by bisection in LDS.
+__global__ __launch_bounds__(kSortThreads) void bucket_count_kernel(
+    const uint64_t* __restrict__ key, int64_t n, int ntiles, const uint64_t* __restrict__ skey,
+    const uint32_t* __restrict__ sidx, uint8_t* __restrict__ digit, uint32_t* __restrict__ counts) {
+  __shared__ uint32_t h[256];
+  __shared__ uint64_t bk[kBuckets];
+  __shared__ uint32_t bi[kBuckets];
+  const int t = threadIdx.x;
+  h[t] = 0;
+  bk[t] = skey[t];
+  bi[t] = sidx[t];
+  __syncthreads();
+  const int64_t t0 = int64_t(blockIdx.x) * kSortTile;
+  const int tn = int(n - t0 < kSortTile ? n - t0 : kSortTile);
+#pragma unroll
+  for (int j = 0; j < kSortKPT; ++j) {
+    const int i = j * kSortThreads + t;
+    if (i < tn) {
+      const uint64_t k = key[t0 + i];
+      const uint32_t id = uint32_t(t0 + i);
+      uint32_t b = 0;
+#pragma unroll
+      for (uint32_t step = kBuckets / 2; step > 0; step /= 2)
+        if (!pair_less(k, id, bk[b + step], bi[b + step])) b += step;
+      digit[t0 + i] = uint8_t(b);
+      atomicAdd(&h[b], 1u);
+    }
+  }
+  __syncthreads();
+  counts[size_t(t) * ntiles + blockIdx.x] = h[t];
+}
+
 // counts[d * ntiles + b] -> exclusive prefix over tiles b of digit d (in place);
 // totals[d] = keys with digit d.  One workgroup per digit.
 __global__ __launch_bounds__(256) void radix_digit_scan_kernel(uint32_t* __restrict__ counts, int ntiles,
@@ -178,10 +311,13 @@ __global__ __launch_bounds__(256) void radix_digit_scan_kernel(uint32_t* __restr
 // writes its own row of counts, in program order, so no barrier is needed), placed in
 // digit order in LDS, and written out so that consecutive threads write consecutive
 // positions of each digit's run.
+// BUCKET: the digit comes from `digit` and the index is the position.
+template <bool BUCKET>
 __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
     const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin, uint64_t* __restrict__ kout,
     uint32_t* __restrict__ vout, int64_t n, int shift, int ntiles, const uint32_t* __restrict__ counts,
-    const uint32_t* __restrict__ totals) {
+    const uint32_t* __restrict__ totals, const uint8_t* __restrict__ digit) {
+  __shared__ uint8_t sd[BUCKET ? kSortTile : 1];
   __shared__ uint64_t sk[kSortTile];
   __shared__ uint32_t sv[kSortTile];
   __shared__ uint32_t cnt[4][256];  // per wavefront: running digit counts, then bases
@@ -195,18 +331,24 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
   const int tn = int(n - t0 < kSortTile ? n - t0 : kSortTile);  // keys of this tile
   constexpr int Q = kSortTile / 4;
   uint64_t k[kSortKPT];
-  uint32_t v[kSortKPT], rank[kSortKPT];
+  uint32_t v[kSortKPT], rank[kSortKPT], dig[kSortKPT];
 #pragma unroll
   for (int j = 0; j < kSortKPT; ++j) {
     const int i = w * Q + j * 64 + lane;
     k[j] = i < tn ? kin[t0 + i] : 0ull;
-    v[j] = i < tn ? vin[t0 + i] : 0u;
+    if constexpr (BUCKET) {
+      v[j] = uint32_t(t0 + i);
+      dig[j] = i < tn ? digit[t0 + i] : 0u;
+    } else {
+      v[j] = i < tn ? vin[t0 + i] : 0u;
+      dig[j] = uint32_t(k[j] >> shift) & 0xffu;
+    }
   }
   const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
   for (int j = 0; j < kSortKPT; ++j) {
     const bool valid = w * Q + j * 64 + lane < tn;
-    const uint32_t d = uint32_t(k[j] >> shift) & 0xffu;
+    const uint32_t d = dig[j];
     const uint64_t same = same_digit_lanes(d, valid);
     const uint32_t below = uint32_t(__popcll(same & lt_mask));
     uint32_t r = 0;
@@ -235,22 +377,286 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
 #pragma unroll
   for (int j = 0; j < kSortKPT; ++j) {
     if (w * Q + j * 64 + lane < tn) {
-      const uint32_t pos = cnt[w][uint32_t(k[j] >> shift) & 0xffu] + rank[j];
+      const uint32_t pos = cnt[w][dig[j]] + rank[j];
       if (pos < uint32_t(kSortTile)) {  // always true; keeps a logic error inside the tile
         sk[pos] = k[j];
         sv[pos] = v[j];
+        if constexpr (BUCKET) sd[pos] = uint8_t(dig[j]);
       }
     }
   }
   __syncthreads();
   for (int i = t; i < tn; i += kSortThreads) {
     const uint64_t kk = sk[i];
-    const uint32_t pos = gbase[uint32_t(kk >> shift) & 0xffu] + uint32_t(i);
+    const uint32_t pos = gbase[BUCKET ? uint32_t(sd[BUCKET ? i : 0]) : uint32_t(kk >> shift) & 0xffu] + uint32_t(i);
     if (int64_t(pos) < n) {  // always true; keeps a logic error inside the output
       kout[pos] = kk;
       vout[pos] = sv[i];
     }
   }
+}
+
+// Sorts one bucket (a workgroup each) by key, stably, and writes its particles' order.
+// A bucket of at most kBucketTile keys stays in LDS and registers: wavefront w holds keys
+// [w Q, (w+1) Q) and ranks them as radix_scatter_kernel does.  A larger one (the samples
+// missed the distribution) takes its passes through memory, tile by tile: slow, but any
+// input is sorted.  (k0, v0): the keys and indices by bucket; (k1, v1): scratch; the order
+// is written to v1.
+__global__ __launch_bounds__(kBucketThreads) void bucket_sort_kernel(uint64_t* k0, uint32_t* v0, uint64_t* k1,
+                                                                     uint32_t* v1, int64_t n,
+                                                                     const uint32_t* __restrict__ totals) {
+  uint32_t* perm = v1;  // (a large bucket is done with the buffer before its order is written)
+  constexpr int kWaves = kBucketThreads / 64;
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  uint64_t* sk = reinterpret_cast<uint64_t*>(lds_raw);                       // [kBucketTile]
+  uint32_t* sv = reinterpret_cast<uint32_t*>(sk + kBucketTile);              // [kBucketTile]
+  uint32_t(*cnt)[256] = reinterpret_cast<uint32_t(*)[256]>(sv + kBucketTile);  // [kWaves][256]
+  __shared__ uint32_t base[256], wsum[4];
+  __shared__ unsigned long long kmin_s, kmax_s;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  if (t == 0) {
+    kmin_s = ~0ull;
+    kmax_s = 0ull;
+  }
+  // first key of the bucket: the totals of the buckets before it
+  if (t < 256) {
+    const uint32_t mine = t < int(blockIdx.x) ? totals[t] : 0u;
+    uint32_t sum = mine;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    if (lane == 0) wsum[w] = sum;
+  }
+  __syncthreads();
+  const int64_t b0 = int64_t(wsum[0]) + wsum[1] + wsum[2] + wsum[3];
+  int64_t m = totals[blockIdx.x];
+  if (b0 + m > n) m = n > b0 ? n - b0 : 0;  // never: keeps a logic error inside the arrays
+  if (m == 0) return;
+  k0 += b0;
+  v0 += b0;
+  k1 += b0;
+  v1 += b0;
+  perm += b0;
+  const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  // Keys are taken from the smallest one on: their span tells which digits matter (their
+  // common bits would not: a bucket may lie across a power of two)
+  {
+    unsigned long long lo = ~0ull, hi = 0ull;
+    for (int64_t i = t; i < m; i += kBucketThreads) {
+      const unsigned long long x = k0[i];
+      lo = x < lo ? x : lo;
+      hi = x > hi ? x : hi;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const unsigned long long a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
+      lo = a < lo ? a : lo;
+      hi = b > hi ? b : hi;
+    }
+    if (lane == 0 && t < m) {
+      atomicMin(&kmin_s, lo);
+      atomicMax(&kmax_s, hi);
+    }
+  }
+  __syncthreads();
+  const uint64_t kmin = kmin_s, span = kmax_s - kmin;
+  const int top = span ? 64 - __clzll(static_cast<long long>(span)) : 0;  // the keys' bits
+
+  // exclusive start of every digit from the counts of the wavefronts (one pass over a tile):
+  // cnt[w][d] <- first position of wavefront w's keys of digit d
+  auto starts = [&]() __attribute__((always_inline)) {
+    uint32_t own = 0;
+    if (t < 256)
+#pragma unroll
+      for (int q = 0; q < kWaves; ++q) own += cnt[q][t];
+    uint32_t incl = own;
+    if (t < 256) {
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(incl, o);
+        if (lane >= o) incl += y;
+      }
+      if (lane == 63) wsum[w] = incl;
+    }
+    __syncthreads();
+    if (t < 256) {
+      uint32_t run = incl - own;
+      for (int q = 0; q < w; ++q) run += wsum[q];
+#pragma unroll
+      for (int q = 0; q < kWaves; ++q) {
+        const uint32_t c = cnt[q][t];
+        cnt[q][t] = run;
+        run += c;
+      }
+    }
+    __syncthreads();
+  };
+  // ranks of the keys of a tile of tn keys (rounds of 64 a wavefront) in their wavefront
+  uint64_t k[kBucketKPT];
+  uint32_t v[kBucketKPT], rank[kBucketKPT];
+  auto rank_tile = [&](int tn, int rounds, int shift) __attribute__((always_inline)) {
+    for (int i = t; i < kWaves * 256; i += kBucketThreads) (&cnt[0][0])[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kBucketKPT; ++j) {
+      if (j < rounds) {
+        const bool valid = (w * rounds + j) * 64 + lane < tn;
+        const uint32_t d = uint32_t(k[j] >> shift) & 0xffu;
+        const uint64_t same = same_digit_lanes(d, valid);
+        const uint32_t below = uint32_t(__popcll(same & lt_mask));
+        uint32_t r = 0;
+        if (valid) {
+          r = cnt[w][d];
+          if (below == 0) cnt[w][d] = r + uint32_t(__popcll(same));
+        }
+        rank[j] = r + below;
+      }
+    }
+    __syncthreads();
+  };
+
+  if (m <= kBucketTile) {
+    const int tn = int(m);
+    const int rounds = (tn + kBucketThreads - 1) / kBucketThreads;
+#pragma unroll
+    for (int j = 0; j < kBucketKPT; ++j) {
+      const int i = (w * rounds + j) * 64 + lane;
+      if (j < rounds) {
+        k[j] = i < tn ? k0[i] - kmin : 0ull;
+        v[j] = i < tn ? v0[i] : 0u;
+      }
+    }
+    auto pass = [&](int shift) __attribute__((always_inline)) {
+      rank_tile(tn, rounds, shift);
+      starts();
+#pragma unroll
+      for (int j = 0; j < kBucketKPT; ++j) {
+        if (j < rounds && (w * rounds + j) * 64 + lane < tn) {
+          const uint32_t pos = cnt[w][uint32_t(k[j] >> shift) & 0xffu] + rank[j];
+          if (pos < uint32_t(kBucketTile)) {  // always true; keeps a logic error inside the tile
+            sk[pos] = k[j];
+            sv[pos] = v[j];
+          }
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < kBucketKPT; ++j) {
+        const int i = (w * rounds + j) * 64 + lane;
+        if (j < rounds && i < tn) {
+          k[j] = sk[i];
+          v[j] = sv[i];
+        }
+      }
+      __syncthreads();
+    };
+    if (top > 16) {
+      // The 16 highest of them leave few keys of a bucket equal: two passes, then
+      // every key counts the smaller ones among those that share these bits, which now
+      // stand side by side.  A long run of them (kRunMost on a side) takes all passes.
+      constexpr int kRunMost = 24;
+      const int lo = top - 16;
+      pass(lo);
+      pass(lo + 8);
+      if (t == 0) base[0] = 0;
+      __syncthreads();
+      bool too_long = false;
+      static_for<kBucketKPT>([&](auto jc) {  // (the loops inside keep a for from unrolling)
+        constexpr int j = decltype(jc)::value;
+        const int i = (w * rounds + j) * 64 + lane;
+        if (j < rounds && i < tn) {
+          const uint64_t mine = k[j], run = mine >> lo;
+          int s = i, before = 0, e = i + 1;
+          while (s > 0 && i - s < kRunMost && (sk[s - 1] >> lo) == run) {
+            --s;
+            before += sk[s] <= mine ? 1 : 0;
+          }
+          while (e < tn && e - i < kRunMost && (sk[e] >> lo) == run) {
+            before += sk[e] < mine ? 1 : 0;
+            ++e;
+          }
+          too_long = too_long || i - s >= kRunMost || e - i >= kRunMost;
+          rank[j] = uint32_t(s + before);
+        }
+      });
+      if (too_long) base[0] = 1;
+      __syncthreads();
+      if (base[0] == 0) {
+#pragma unroll
+        for (int j = 0; j < kBucketKPT; ++j) {
+          const int i = (w * rounds + j) * 64 + lane;
+          if (j < rounds && i < tn) perm[rank[j]] = v[j];
+        }
+        return;
+      }
+    }
+    for (int shift = 0; shift < top; shift += 8) pass(shift);
+#pragma unroll
+    for (int j = 0; j < kBucketKPT; ++j) {
+      const int i = (w * rounds + j) * 64 + lane;
+      if (j < rounds && i < tn) perm[i] = v[j];
+    }
+    return;
+  }
+
+  uint64_t *ka = k0, *kb = k1;
+  uint32_t *va = v0, *vb = v1;
+  for (int shift = 0; shift < top; shift += 8) {
+    // base[d]: where the next key of digit d goes
+    if (t < 256) base[t] = 0;
+    __syncthreads();
+    for (int64_t i = t; i < m; i += kBucketThreads) atomicAdd(&base[uint32_t((ka[i] - kmin) >> shift) & 0xffu], 1u);
+    __syncthreads();
+    if (t == 0) {
+      uint32_t run = 0;
+      for (int d = 0; d < 256; ++d) {
+        const uint32_t c = base[d];
+        base[d] = run;
+        run += c;
+      }
+    }
+    __syncthreads();
+    for (int64_t t0 = 0; t0 < m; t0 += kBucketTile) {
+      const int tn = int(m - t0 < kBucketTile ? m - t0 : kBucketTile);
+#pragma unroll
+      for (int j = 0; j < kBucketKPT; ++j) {
+        const int i = (w * kBucketKPT + j) * 64 + lane;
+        k[j] = i < tn ? ka[t0 + i] - kmin : 0ull;
+        v[j] = i < tn ? va[t0 + i] : 0u;
+      }
+      rank_tile(tn, kBucketKPT, shift);
+      // positions within the digit: the wavefronts' counts before this one's
+      uint32_t own = 0;
+      if (t < 256) {
+        for (int q = 0; q < kWaves; ++q) {
+          const uint32_t c = cnt[q][t];
+          cnt[q][t] = base[t] + own;
+          own += c;
+        }
+        base[t] += own;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < kBucketKPT; ++j) {
+        if ((w * kBucketKPT + j) * 64 + lane < tn) {
+          const uint32_t pos = cnt[w][uint32_t(k[j] >> shift) & 0xffu] + rank[j];
+          if (int64_t(pos) < m) {  // always true; keeps a logic error inside the bucket
+            kb[pos] = k[j] + kmin;
+            vb[pos] = v[j];
+          }
+        }
+      }
+      __syncthreads();
+    }
+    __threadfence_block();
+    __syncthreads();
+    uint64_t* tk = ka;
+    ka = kb;
+    kb = tk;
+    uint32_t* tv = va;
+    va = vb;
+    vb = tv;
+  }
+  for (int64_t i = t; i < m; i += kBucketThreads) perm[i] = va[i];
 }
 
 // ------------------------------------------------------------------ basis
@@ -587,7 +993,7 @@ __global__ __launch_bounds__(256) void mex_tile_offsets_kernel(const MexArgs<LB>
   for (int c = threadIdx.x; c < 2 * ncu; c += blockDim.x) {
     const int side = c < ncu ? 0 : 1;
     const int comp = side == 0 ? c : c - ncu;
-    double run = a.bsum[(size_t(b) * 2 + side) * NC + comp];
+    double run = a.nblocks > 1 ? a.bsum[(size_t(b) * 2 + side) * NC + comp] : 0.0;
     for (int k = t0; k < t1; ++k) {
       const int tl = side == 0 ? k : t1 - 1 - (k - t0);
       const size_t o = (size_t(tl) * 2 + side) * NC + comp;
@@ -886,6 +1292,11 @@ __global__ __launch_bounds__(kMexTile, LB <= 10 ? 3 : 2) void mex_force_staged_k
 // ================================================================ host side
 namespace {
 
+// the whole 160 KiB of a CU may be requested as LDS (failures surface at the launch)
+void set_lds_limit(const void* kfn) {
+  (void)hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
+}
+
 struct MexLayout {
   size_t off_key0, off_key1, off_idx0, off_idx1, off_sort, sort_bytes, off_tsum, off_toff, off_bsum,
       total;
@@ -935,9 +1346,11 @@ int launch_mex_lb(const MexArgs<LB>& a, int ntiles, hipStream_t st) {
     hipLaunchKernelGGL((mex_tile_sums_kernel<T, LB>), dim3(ntiles), dim3(kMexTile), lds_sums, st, a);
   int rc = hip_fail(hipGetLastError(), "mex_tile_sums_kernel launch");
   if (rc) return rc;
-  hipLaunchKernelGGL((mex_block_sums_kernel<LB>), dim3(a.nblocks), dim3(256), 0, st, a);
-  const int ncol = 2 * (a.lmax + 1) * (a.lmax + 1);
-  hipLaunchKernelGGL((mex_block_scan_kernel<LB>), dim3((ncol + 3) / 4), dim3(256), 0, st, a);
+  if (a.nblocks > 1) {  // (a single block of tiles has nothing before or after it)
+    hipLaunchKernelGGL((mex_block_sums_kernel<LB>), dim3(a.nblocks), dim3(256), 0, st, a);
+    const int ncol = 2 * (a.lmax + 1) * (a.lmax + 1);
+    hipLaunchKernelGGL((mex_block_scan_kernel<LB>), dim3((ncol + 3) / 4), dim3(256), 0, st, a);
+  }
   hipLaunchKernelGGL((mex_tile_offsets_kernel<LB>), dim3(a.nblocks), dim3(256), 0, st, a);
   rc = hip_fail(hipGetLastError(), "mex tile offset launch");
   if (rc) return rc;
@@ -1006,16 +1419,46 @@ int launch_mex_force(const double* x, const double* y, const double* z, const do
   double* toff = reinterpret_cast<double*>(base + L.off_toff);
   double* bsum = reinterpret_cast<double*>(base + L.off_bsum);
 
-  hipLaunchKernelGGL(mex_keys_kernel, dim3(int((n + 255) / 256)), dim3(256), 0, st, x, y, z, n, k0, i0);
-  int rc = hip_fail(hipGetLastError(), "mex_keys_kernel launch");
-  if (rc) return rc;
-  for (int pass = 0; pass < kSortPasses; ++pass) {
+  int rc = ETICS_OK;
+  if (n <= kRankMost) {
+    const size_t lds = size_t(n) * 8;
+    set_lds_limit(reinterpret_cast<const void*>(mex_rank_kernel));
+    hipLaunchKernelGGL(mex_rank_kernel, dim3(int((n + kRankTargets - 1) / kRankTargets)), dim3(kRankThreads), lds, st,
+                       x, y, z, int(n), i0);
+    rc = hip_fail(hipGetLastError(), "mex_rank_kernel launch");
+    if (rc) return rc;
+  } else if (n <= kSampleMost) {
+    // the splitters and the buckets of the keys lie where the tile sums and offsets come
+    // to lie afterwards (at least 9 n / 8 bytes each)
+    uint8_t* digit = reinterpret_cast<uint8_t*>(tsum);
+    uint64_t* skey = reinterpret_cast<uint64_t*>(toff);
+    uint32_t* sidx = reinterpret_cast<uint32_t*>(skey + kBuckets);
+    hipLaunchKernelGGL(mex_keys_kernel, dim3(int((n + 255) / 256)), dim3(256), 0, st, x, y, z, n, k0,
+                       static_cast<uint32_t*>(nullptr));
+    hipLaunchKernelGGL(mex_splitters_kernel, dim3(kSamples / kRankTargets), dim3(kSplitThreads), 0, st, k0, n, skey,
+                       sidx);
+    hipLaunchKernelGGL(bucket_count_kernel, dim3(L.stiles), dim3(kSortThreads), 0, st, k0, n, L.stiles, skey, sidx,
+                       digit, counts);
+    hipLaunchKernelGGL(radix_digit_scan_kernel, dim3(256), dim3(256), 0, st, counts, L.stiles, totals);
+    hipLaunchKernelGGL(radix_scatter_kernel<true>, dim3(L.stiles), dim3(kSortThreads), 0, st, k0,
+                       static_cast<const uint32_t*>(nullptr), k1, i1, n, 0, L.stiles, counts, totals, digit);
+    set_lds_limit(reinterpret_cast<const void*>(bucket_sort_kernel));
+    constexpr size_t lds = size_t(kBucketTile) * 12 + size_t(kBucketThreads / 64) * 256 * 4;
+    hipLaunchKernelGGL(bucket_sort_kernel, dim3(kBuckets), dim3(kBucketThreads), lds, st, k1, i1, k0, i0, n, totals);
+    rc = hip_fail(hipGetLastError(), "sample sort launch");
+    if (rc) return rc;
+  } else {
+    hipLaunchKernelGGL(mex_keys_kernel, dim3(int((n + 255) / 256)), dim3(256), 0, st, x, y, z, n, k0, i0);
+    rc = hip_fail(hipGetLastError(), "mex_keys_kernel launch");
+    if (rc) return rc;
+  }
+  for (int pass = 0; pass < (n > kSampleMost ? kSortPasses : 0); ++pass) {
     const int shift = 8 * pass;
     hipLaunchKernelGGL(radix_count_kernel, dim3(L.stiles), dim3(kSortThreads), 0, st, k0, n, shift, L.stiles,
                        counts);
     hipLaunchKernelGGL(radix_digit_scan_kernel, dim3(256), dim3(256), 0, st, counts, L.stiles, totals);
-    hipLaunchKernelGGL(radix_scatter_kernel, dim3(L.stiles), dim3(kSortThreads), 0, st, k0, i0, k1, i1, n,
-                       shift, L.stiles, counts, totals);
+    hipLaunchKernelGGL(radix_scatter_kernel<false>, dim3(L.stiles), dim3(kSortThreads), 0, st, k0, i0, k1, i1, n,
+                       shift, L.stiles, counts, totals, static_cast<const uint8_t*>(nullptr));
     rc = hip_fail(hipGetLastError(), "radix sort launch");
     if (rc) return rc;
     uint64_t* tk = k0;
