@@ -122,11 +122,21 @@ double anl_tilde(int n, int l, int basis) {
 }
 
 namespace {
+// -sqrt(4 pi) Atilde_nl k_n of every order up to the caps, computed once: four lgamma, an
+// exp and a product per (n, l) were up to 90 us of host time in every coefficient call
+struct ScaleTable {
+  double v[2][NCAP + 1][LCAP + 1];
+  ScaleTable() {
+    for (int b = 0; b < 2; ++b)
+      for (int nn = 0; nn <= NCAP; ++nn)
+        for (int l = 0; l <= LCAP; ++l)
+          v[b][nn][l] = -2.0 * std::sqrt(kPi) * anl_tilde(nn, l, b) * gegen_k(nn, basis_alpha(b, l));
+  }
+};
 void fill_scale(double* scale, int nmax, int lmax, int basis) {
+  static const ScaleTable table;
   for (int nn = 0; nn <= nmax; ++nn)
-    for (int l = 0; l <= lmax; ++l)
-      scale[nn * (lmax + 1) + l] =
-          -2.0 * std::sqrt(kPi) * anl_tilde(nn, l, basis) * gegen_k(nn, basis_alpha(basis, l));
+    for (int l = 0; l <= lmax; ++l) scale[nn * (lmax + 1) + l] = table.v[basis][nn][l];
 }
 
 }  // namespace
