@@ -66,9 +66,12 @@ __global__ __launch_bounds__(256) void scf_force_prep_kernel(const double* __res
   c[K + k] = su * b;
 }
 
-// FP32: the quad layout of RadialMM, one thread per value
+// FP32: the quad layout of RadialMM, one thread per value; with Ad, Bd (the jerk) each
+// system's coefficients are followed by their time derivatives
 __global__ __launch_bounds__(256) void scf_force_prep_mm_kernel(const double* __restrict__ A,
                                                                const double* __restrict__ B,
+                                                               const double* __restrict__ Ad,
+                                                               const double* __restrict__ Bd,
                                                                int nmax, int lmax, int nsys, int basis,
                                                                float* __restrict__ cf) {
   const int Q = mm_offset(lmax + 1, nmax);
@@ -87,15 +90,18 @@ __global__ __launch_bounds__(256) void scf_force_prep_mm_kernel(const double* __
   // run 0: order 0 of U, V; then per pair j: U, V of 1+2j, of 2+2j, W, X of 1+2j, of 2+2j
   const int n = run == 0 ? 0 : 1 + 2 * ((run - 1) / 4) + ((run - 1) & 1);
   const bool deriv = run > 0 && (((run - 1) >> 1) & 1);
-  float v = 0.f;
+  float v = 0.f, d = 0.f;
   if (n <= nmax && slot <= 2 * l) {
     const int m = slot <= l ? slot : slot - l;
     const int K = (nmax + 1) * (lmax + 1) * (lmax + 2) / 2;
     const int64_t k = int64_t(sys) * K + n * ((lmax + 1) * (lmax + 2) / 2) + l * (l + 1) / 2 + m;
     const double scale = deriv ? g_force_scales.sw[basis][n][l] : g_force_scales.su[basis][n][l];
     v = float(scale * (slot <= l ? A[k] : B[k]));
+    if (Ad) d = float(scale * (slot <= l ? Ad[k] : Bd[k]));
   }
-  cf[g] = v;
+  float* const c = cf + size_t(sys) * (Ad ? 2 * Q : Q);
+  c[g - int64_t(sys) * Q] = v;
+  if (Ad) c[Q + (g - int64_t(sys) * Q)] = d;
 }
 
 // ------------------------------------------------------------------------ force
@@ -149,7 +155,7 @@ __device__ __forceinline__ void force_store(const ForceArgs& a, int64_t i, T pot
 template <int LB, bool ACC, int BASIS, bool NEXT>
 __device__ __forceinline__ void force_points_mm(const ForceArgs& a, const float* cf, int64_t i0, int64_t i1,
                                                 int64_t stride) {
-  RadialMM<ACC, BASIS> rad(cf, a.nmax, a.lmax);
+  RadialMM<float, ACC, BASIS> rad(cf, a.nmax, a.lmax);
   double x = 0.0, y = 0.0, z = 0.0;
   auto load = [&](int64_t i) {
     const bool valid = i < i1;
@@ -254,6 +260,14 @@ __global__ __launch_bounds__(256, sizeof(T) == 8 ? (LB <= 6 ? 3 : 2) : LB <= 10 
   }
 }
 
+int launch_force_prep_mm(const double* A, const double* B, const double* Ad, const double* Bd, int nmax, int lmax,
+                         int nsys, int basis, float* cf, hipStream_t st) {
+  const int64_t values = int64_t(nsys) * mm_offset(lmax + 1, nmax);
+  hipLaunchKernelGGL(scf_force_prep_mm_kernel, dim3(unsigned((values + 255) / 256)), dim3(256), 0, st, A, B, Ad, Bd,
+                     nmax, lmax, nsys, basis, cf);
+  return hip_fail(hipGetLastError(), "scf_force_prep_mm_kernel launch");
+}
+
 size_t force_prep_bytes(int nmax, int lmax, int prec) {
   return prec == ETICS_FP64 ? size_t(2) * coeff_count(nmax, lmax) * 8 : size_t(mm_offset(lmax + 1, nmax)) * 4;
 }
@@ -354,8 +368,7 @@ int launch_prep(const double* A, const double* B, int nmax, int lmax, int nsys, 
     hipLaunchKernelGGL(scf_force_prep_kernel, dim3(pb), dim3(256), 0, st, A, B, nmax, lmax, nsys, basis,
                        reinterpret_cast<double*>(ws));
   else
-    hipLaunchKernelGGL(scf_force_prep_mm_kernel, dim3(pb), dim3(256), 0, st, A, B, nmax, lmax, nsys, basis,
-                       reinterpret_cast<float*>(ws));
+    return launch_force_prep_mm(A, B, nullptr, nullptr, nmax, lmax, nsys, basis, reinterpret_cast<float*>(ws), st);
   return hip_fail(hipGetLastError(), "scf_force_prep_kernel launch");
 }
 

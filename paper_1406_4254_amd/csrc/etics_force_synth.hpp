@@ -210,37 +210,77 @@ struct RadialF64 {
 // (10, 6): 25 -> 16 us.  Coefficient loads through 64-bit vector addresses kept one
 // address pair per l in registers (181 VGPRs, two wavefronts per SIMD: 109 us), and
 // recurrence constants through scalar loads left a wait in every pair (100 us).
+//
+// With T = Dual<float> (the jerk) every value carries its time derivative: a quad has a
+// second accumulator, to which (coefficient) x (recurrence value)' and (coefficient)' x
+// (recurrence value) go in turn, as in the Dual FMA; the derivatives of the coefficients
+// are a second array of the same layout behind the first.
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 template <int BLOCK>
 __device__ __forceinline__ f32x4_t mfma_quad(float a, float b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, BLOCK, 0);
 }
+template <int BLOCK>
+__device__ __forceinline__ Dual<f32x4_t> mfma_quad(Dual<float> a, Dual<float> b, Dual<f32x4_t> c) {
+  return {mfma_quad<BLOCK>(a.v, b.v, c.v), mfma_quad<BLOCK>(a.v, b.d, c.d)};
+}
+// the second part of a derivative's sum, apart from the first so that instructions on other
+// quads stand between them
+template <int BLOCK>
+__device__ __forceinline__ void mfma_rest(float, float, f32x4_t&) {}
+template <int BLOCK>
+__device__ __forceinline__ void mfma_rest(Dual<float> a, Dual<float> b, Dual<f32x4_t>& c) {
+  c.d = mfma_quad<BLOCK>(a.d, b.v, c.d);
+}
+template <typename T>
+struct QuadOf {
+  using type = f32x4_t;
+  static __device__ __forceinline__ type zero() { return f32x4_t{0.f, 0.f, 0.f, 0.f}; }
+  static __device__ __forceinline__ float get(const type& q, int i) { return q[i]; }
+};
+template <>
+struct QuadOf<Dual<float>> {
+  using type = Dual<f32x4_t>;
+  static __device__ __forceinline__ type zero() { return {QuadOf<float>::zero(), QuadOf<float>::zero()}; }
+  static __device__ __forceinline__ Dual<float> get(const type& q, int i) { return {q.v[i], q.d[i]}; }
+};
 __host__ __device__ constexpr int mm_quads(int l) { return slot_pad(l, 4) / 4; }
 // pairs of orders from order 1 on (at least one, so the first needs no branch)
 __host__ __device__ constexpr int mm_pairs(int nmax) { return nmax < 1 ? 1 : (nmax + 1) / 2; }
 // floats of the l's before l, and of the whole array (l = lmax + 1)
 __host__ __device__ constexpr int mm_offset(int l, int nmax) { return zoff(l, 4) * (1 + 4 * mm_pairs(nmax)); }
 
-template <bool ACC, int BASIS>
+template <typename T, bool ACC, int BASIS>
 struct RadialMM {
+  static_assert(ACC || sizeof(T) == 4, "a Dual potential alone is not instantiated");
+  using Quad = typename QuadOf<T>::type;
+  static constexpr bool kDual = sizeof(T) == 8;
   // The coefficients through a buffer descriptor: its base and the position are scalar,
   // so a lane keeps one offset register for every load, and the lanes past the values of
   // a short run read the following ones, or zero past the array's end.
   __amdgpu_buffer_rsrc_t cf;
   int nmax, lane4;        // lane4: the lane's byte offset
+  int der;                // Dual: position of the derivatives' array
   int pos;                // start of the current l
   // this lane's coefficients: order 0; the next two pairs of orders (U, V and W, X)
-  float a0, x0, y0, x1, y1;
+  T a0, x0, y0, x1, y1;
 
   // cfp: the prepared coefficients of one system, the same pointer in every lane
   __device__ __forceinline__ RadialMM(const float* cfp, int nmax_, int lmax_)
-      : cf(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(cfp), 0, 4 * mm_offset(lmax_ + 1, nmax_),
-                                             0x00020000)),
-        nmax(nmax_), lane4(4 * int(threadIdx.x & 63)), pos(0), a0(0.f), x0(0.f), y0(0.f), x1(0.f), y1(0.f) {}
+      : cf(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(cfp), 0,
+                                             (kDual ? 8 : 4) * mm_offset(lmax_ + 1, nmax_), 0x00020000)),
+        nmax(nmax_), lane4(4 * int(threadIdx.x & 63)), der(mm_offset(lmax_ + 1, nmax_)), pos(0), a0(T(0.f)),
+        x0(T(0.f)), y0(T(0.f)), x1(T(0.f)), y1(T(0.f)) {}
 
-  // this lane's float at position pos + off
-  __device__ __forceinline__ float load(int off) const {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(cf, lane4, 4 * (pos + off), 0));
+  // this lane's value at position pos + off
+  __device__ __forceinline__ float load1(int at) const {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(cf, lane4, 4 * at, 0));
+  }
+  __device__ __forceinline__ T load(int off) const {
+    if constexpr (kDual)
+      return T(load1(pos + off), load1(pos + off + der));
+    else
+      return load1(pos + off);
   }
   // one register holds a pair's U, V and W, X quads if they are at most 16
   template <int l>
@@ -248,7 +288,7 @@ struct RadialMM {
 
   // pair J of the orders of l (past the last pair: other values, not used)
   template <int l, int J>
-  __device__ __forceinline__ void load_pair(float& x, float& y) const {
+  __device__ __forceinline__ void load_pair(T& x, T& y) const {
     constexpr int at = 4 * mm_quads(l) * (1 + 4 * J);
     x = load(at);
     if constexpr (ACC && !one_reg<l>()) y = load(at + 8 * mm_quads(l));
@@ -263,19 +303,19 @@ struct RadialMM {
   }
 
   template <int l>
-  __device__ __forceinline__ void sums(float xi, float (&U)[l + 1], float (&V)[l + 1], float (&W)[l + 1],
-                                       float (&X)[l + 1]) {
+  __device__ __forceinline__ void sums(T xi, T (&U)[l + 1], T (&V)[l + 1], T (&W)[l + 1], T (&X)[l + 1]) {
     constexpr int NQ = mm_quads(l);
-    const f32x4_t zero{0.f, 0.f, 0.f, 0.f};
-    f32x4_t uv[NQ], wx[NQ];
+    const Quad zero = QuadOf<T>::zero();
+    Quad uv[NQ], wx[NQ];
     static_for<NQ>([&](auto qc) {
       constexpr int q = decltype(qc)::value;
-      uv[q] = mfma_quad<q>(a0, 1.0f, zero);
+      uv[q] = mfma_quad<q>(a0, T(1.f), zero);
+      mfma_rest<q>(a0, T(1.f), uv[q]);
     });
-    float c2 = 0.f, c1 = 1.f;  // Chat_{n-2}, Chat_{n-1} for n = 1
-    float e2 = 0.f, e1 = 1.f;  // Ehat_{n-2}, Ehat_{n-1}
+    T c2 = T(0.f), c1 = T(1.f);  // Chat_{n-2}, Chat_{n-1} for n = 1
+    T e2 = T(0.f), e1 = T(1.f);  // Ehat_{n-2}, Ehat_{n-1}
     // order NN: c <- Chat_NN, accumulate, advance Ehat
-    auto step = [&](auto nc, float x, float y, float& cA, float& cB, float& eA, float& eB) {
+    auto step = [&](auto nc, T x, T y, T& cA, T& cB, T& eA, T& eB) {
       constexpr int NN = decltype(nc)::value;
       constexpr int PAR = (NN - 1) % 2;
       constexpr float q = float(BASIS == kBasisCB ? kTab.qcb[l][NN] : kTab.q[l][NN]);
@@ -288,12 +328,25 @@ struct RadialMM {
       if constexpr (ACC) {
         static_for<NQ>([&](auto qc) {
           constexpr int b = decltype(qc)::value;
-          const f32x4_t w = NN == 1 ? zero : wx[b];
+          const Quad w = NN == 1 ? zero : wx[b];
           if constexpr (one_reg<l>())
             wx[b] = mfma_quad<(2 + PAR) * NQ + b>(x, eB, w);
           else
             wx[b] = mfma_quad<PAR * NQ + b>(y, eB, w);
         });
+        if constexpr (kDual) {
+          static_for<NQ>([&](auto qc) {
+            constexpr int b = decltype(qc)::value;
+            mfma_rest<PAR * NQ + b>(x, cA, uv[b]);
+          });
+          static_for<NQ>([&](auto qc) {
+            constexpr int b = decltype(qc)::value;
+            if constexpr (one_reg<l>())
+              mfma_rest<(2 + PAR) * NQ + b>(x, eB, wx[b]);
+            else
+              mfma_rest<PAR * NQ + b>(y, eB, wx[b]);
+          });
+        }
         eA = recur(xi, eB, qd, eA);
       }
     };
@@ -308,8 +361,8 @@ struct RadialMM {
     asm volatile("" : "+s"(npairs));
     auto pairs = [&](auto self, auto jc) -> void {
       constexpr int J = decltype(jc)::value;
-      float& x = J % 2 ? x1 : x0;
-      float& y = J % 2 ? y1 : y0;
+      T& x = J % 2 ? x1 : x0;
+      T& y = J % 2 ? y1 : y0;
       step(std::integral_constant<int, 1 + 2 * J>{}, x, y, c2, c1, e2, e1);
       step(std::integral_constant<int, 2 + 2 * J>{}, x, y, c1, c2, e1, e2);
       if constexpr (J + 2 < mm_pairs(NCAP)) load_pair<l, J + 2>(x, y);
@@ -321,10 +374,10 @@ struct RadialMM {
     pos += 4 * NQ * (1 + 4 * npairs);
 #pragma unroll
     for (int m = 0; m <= l; ++m) {
-      U[m] = uv[m / 4][m % 4];
-      W[m] = wx[m / 4][m % 4];
-      V[m] = m > 0 ? uv[(l + m) / 4][(l + m) % 4] : 0.f;
-      X[m] = m > 0 ? wx[(l + m) / 4][(l + m) % 4] : 0.f;
+      U[m] = QuadOf<T>::get(uv[m / 4], m % 4);
+      W[m] = QuadOf<T>::get(wx[m / 4], m % 4);
+      V[m] = m > 0 ? QuadOf<T>::get(uv[(l + m) / 4], (l + m) % 4) : T(0.f);
+      X[m] = m > 0 ? QuadOf<T>::get(wx[(l + m) / 4], (l + m) % 4) : T(0.f);
     }
   }
 };

@@ -90,6 +90,10 @@ int launch_scf_coeffs_dot_batched(const CoeffPlan& p, const double* x, const dou
                                   const int* ustart, const int* usys, int nsys, int64_t ntotal,
                                   double* Ad, double* Bd, void* partials, hipStream_t st);
 size_t jerk_prep_bytes(int nmax, int lmax, int prec);
+// FP32 coefficients prepared for the matrix cores (etics_force.hip), per system, followed
+// by their time derivatives unless Ad, Bd are NULL
+int launch_force_prep_mm(const double* A, const double* B, const double* Ad, const double* Bd, int nmax, int lmax,
+                         int nsys, int basis, float* cf, hipStream_t st);
 // acceleration and jerk at (x, v) from A, B and their time derivatives (etics_jerk.hip)
 int launch_scf_jerk(const double* x, const double* y, const double* z, const double* vx,
                     const double* vy, const double* vz, int64_t n, int nmax, int lmax,

@@ -35,8 +35,9 @@
 namespace etics {
 
 // ---------------------------------------------------------------- coefficient prep
-// Prepared coefficients with their time derivatives, Dual<S> [4K] per system, the same
-// scaling as the force pass (Hernquist-Ostriker basis):
+// FP64: prepared coefficients with their time derivatives, Dual<S> [4K] per system, the
+// same scaling as the force pass (Hernquist-Ostriker basis); FP32: the force pass's own
+// preparation (etics_force.hip), for the matrix cores.
 //   [0,K)   (su A, su dA/dt)   [K,2K)  (su B, su dB/dt)
 //   [2K,3K) (sw A, sw dA/dt)   [3K,4K) (sw B, sw dB/dt)
 template <typename S>
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(256) void scf_jerk_prep_kernel(const double* __rest
 }
 
 size_t jerk_prep_bytes(int nmax, int lmax, int prec) {
-  return size_t(8) * coeff_count(nmax, lmax) * (prec == ETICS_FP64 ? 8 : 4);
+  return prec == ETICS_FP64 ? size_t(8) * coeff_count(nmax, lmax) * 8 : size_t(2) * mm_offset(lmax + 1, nmax) * 4;
 }
 
 // ---------------------------------------------------------------- jerk pass
@@ -91,13 +92,9 @@ struct JerkArgs {
   double dt;
 };
 
-// cf: the prepared coefficients through the constant address space ([4][K]) or in LDS
-// (LdsPtr, QUAD: [K][4])
-template <typename S, int LB, typename CP = ConstPtr<Dual<S>>, bool QUAD = false>
-__device__ __forceinline__ void jerk_point(const JerkArgs& a, CP cf, int64_t i) {
-  const Sph<Dual<S>> s = sph_dual<S, kBasisHO>(a.x[i], a.y[i], a.z[i], a.vx[i], a.vy[i], a.vz[i]);
-  RadialVec<Dual<S>, true, kBasisHO, CP, QUAD> rad{cf, a.K, a.nmax, a.lmax};
-  const ForceOut<Dual<S>> o = synth_point<Dual<S>, LB, true, kBasisHO>(s, rad, a.lmax);
+// point i's acceleration and jerk o go where the mode says
+template <typename S>
+__device__ __forceinline__ void jerk_store(const JerkArgs& a, int64_t i, const ForceOut<Dual<S>>& o) {
   const double g[3] = {double(o.gx.v), double(o.gy.v), double(o.gz.v)};
   const double jk[3] = {double(o.gx.d), double(o.gy.d), double(o.gz.d)};
   double* A[3] = {a.ax, a.ay, a.az};
@@ -114,39 +111,92 @@ __device__ __forceinline__ void jerk_point(const JerkArgs& a, CP cf, int64_t i) 
   double* P[3] = {a.px, a.py, a.pz};
   double* PV[3] = {a.pvx, a.pvy, a.pvz};
   const double dt = a.dt, h = 0.5 * dt, q = dt * dt / 12.0;
+  // all reads before the first write: one wait for them instead of one per component
+  double x[3], v[3], a0[3], j0[3];
+#pragma unroll
   for (int c = 0; c < 3; ++c) {
-    double x = X[c][i], v = V[c][i];
+    x[c] = X[c][i];
+    v[c] = V[c][i];
+    a0[c] = a.mode != kStart ? A[c][i] : 0.0;
+    j0[c] = a.mode != kStart ? J[c][i] : 0.0;
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
     if (a.mode != kStart) {  // corrector with the step's starting a, j
-      const double a0 = A[c][i], j0 = J[c][i];
-      const double v1 = __builtin_fma(q, j0 - jk[c], __builtin_fma(h, a0 + g[c], v));
-      x = __builtin_fma(q, a0 - g[c], __builtin_fma(h, v + v1, x));
-      v = v1;
-      X[c][i] = x;
-      V[c][i] = v;
+      const double v1 = __builtin_fma(q, j0[c] - jk[c], __builtin_fma(h, a0[c] + g[c], v[c]));
+      x[c] = __builtin_fma(q, a0[c] - g[c], __builtin_fma(h, v[c] + v1, x[c]));
+      v[c] = v1;
+      X[c][i] = x[c];
+      V[c][i] = v[c];
     }
     A[c][i] = g[c];
     J[c][i] = jk[c];
     if (a.mode != kLast) {  // predictor of the next step
-      P[c][i] = __builtin_fma(dt * dt * dt / 6.0, jk[c], __builtin_fma(0.5 * dt * dt, g[c], __builtin_fma(dt, v, x)));
-      PV[c][i] = __builtin_fma(0.5 * dt * dt, jk[c], __builtin_fma(dt, g[c], v));
+      P[c][i] = __builtin_fma(dt * dt * dt / 6.0, jk[c],
+                              __builtin_fma(0.5 * dt * dt, g[c], __builtin_fma(dt, v[c], x[c])));
+      PV[c][i] = __builtin_fma(0.5 * dt * dt, jk[c], __builtin_fma(dt, g[c], v[c]));
     }
   }
 }
 
+// The points [i0, i1), one per lane.  FP64: FMAs on coefficients read through the
+// constant address space ([4][K]) or from LDS (LdsPtr, QUAD: [K][4]).
+template <int LB, typename CP, bool QUAD>
+__device__ __forceinline__ void jerk_points_f64(const JerkArgs& a, CP cf, int64_t i0, int64_t i1, int64_t stride) {
+  for (int64_t i = i0 + threadIdx.x; i < i1; i += stride) {
+    const auto s = sph_dual<double, kBasisHO>(a.x[i], a.y[i], a.z[i], a.vx[i], a.vy[i], a.vz[i]);
+    RadialVec<Dual<double>, true, kBasisHO, CP, QUAD> rad{cf, a.K, a.nmax, a.lmax};
+    jerk_store<double>(a, i, synth_point<Dual<double>, LB, true, kBasisHO>(s, rad, a.lmax));
+  }
+}
+// FP32: the radial sums on the matrix cores, which need every lane: the loop is uniform over
+// the workgroup and a lane past the end computes a point at rest at the origin.  At (8, 6)
+// a wavefront issues 3050 VALU and matrix instructions a point instead of 4600, which shows
+// only once the memory traffic of the Hermite step (290 bytes a particle) is asked for in
+// time: a lane's next point and the state to correct are read together, before any write.
+// 256 systems, (8, 6), 5 steps: 10.78 -> 10.02 ms (10.87 with the matrix cores alone).
+template <int LB>
+__device__ __forceinline__ void jerk_points_mm(const JerkArgs& a, const float* cf, int64_t i0, int64_t i1,
+                                               int64_t stride) {
+  RadialMM<Dual<float>, true, kBasisHO> rad(cf, a.nmax, a.lmax);
+  rad.template start<0>();
+  double x, y, z, vx, vy, vz;
+  auto load = [&](int64_t i) {
+    const bool valid = i < i1;
+    x = valid ? a.x[i] : 0.0;
+    y = valid ? a.y[i] : 0.0;
+    z = valid ? a.z[i] : 0.0;
+    vx = valid ? a.vx[i] : 0.0;
+    vy = valid ? a.vy[i] : 0.0;
+    vz = valid ? a.vz[i] : 0.0;
+  };
+  load(i0 + threadIdx.x);
+  for (; i0 < i1; i0 += stride) {
+    const int64_t i = i0 + threadIdx.x;
+    const auto s = sph_dual<float, kBasisHO>(x, y, z, vx, vy, vz);
+    const auto o = synth_point<Dual<float>, LB, true, kBasisHO>(s, rad, a.lmax);
+    // before the stores: loads and stores are waited for in order
+    load(i + stride);
+    rad.template start<0>();
+    if (i < i1) jerk_store<float>(a, i, o);
+  }
+}
+
 template <typename S, int LB>
-__global__ __launch_bounds__(256) void scf_jerk_kernel(const JerkArgs a) {
-  const Dual<S>* __restrict__ cf = reinterpret_cast<const Dual<S>*>(a.cf);
-  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < a.n;
-       i += int64_t(gridDim.x) * blockDim.x)
-    jerk_point<S, LB>(a, ConstPtr<Dual<S>>(cf), i);
+__global__ __launch_bounds__(256, sizeof(S) == 8 ? 1 : LB <= 6 ? 3 : 2) void scf_jerk_kernel(const JerkArgs a) {
+  const int64_t i0 = int64_t(blockIdx.x) * blockDim.x, stride = int64_t(gridDim.x) * blockDim.x;
+  if constexpr (sizeof(S) == 4)
+    jerk_points_mm<LB>(a, reinterpret_cast<const float*>(a.cf), i0, a.n, stride);
+  else
+    jerk_points_f64<LB, ConstPtr<Dual<double>>, false>(
+        a, ConstPtr<Dual<double>>(reinterpret_cast<const Dual<double>*>(a.cf)), i0, a.n, stride);
 }
 
 // batched systems: `split` workgroups per unit of `unit` particles of one system, as the
-// batched force kernel; the workgroup first copies its system's prepared coefficients to
-// LDS as [K][4] and reads them as broadcast VGPR operands (a Dual coefficient would take
-// two SGPRs)
+// batched force kernel; FP64: the workgroup first copies its system's prepared coefficients
+// to LDS as [K][4] and reads them as broadcast VGPR operands
 template <typename S, int LB>
-__global__ __launch_bounds__(256) void scf_jerk_batched_kernel(const JerkArgs a,
+__global__ __launch_bounds__(256, sizeof(S) == 8 ? 1 : LB <= 6 ? 3 : 2) void scf_jerk_batched_kernel(const JerkArgs a,
                                                                const int64_t* __restrict__ offsets,
                                                                const int* __restrict__ ustart,
                                                                const int* __restrict__ usys, int nsys,
@@ -164,16 +214,21 @@ __global__ __launch_bounds__(256) void scf_jerk_batched_kernel(const JerkArgs a,
   const int64_t ue0 = u0 + unit < e ? u0 + unit : e;
   const int64_t ub = u0 + part * kPart < ue0 ? u0 + part * kPart : ue0;
   const int64_t ue = ub + kPart < ue0 ? ub + kPart : ue0;
-  const Dual<S>* __restrict__ cf = reinterpret_cast<const Dual<S>*>(a.cf) + size_t(sys) * 4 * a.K;
-  Dual<S>* lds_cf = reinterpret_cast<Dual<S>*>(jerk_lds);
-  for (int i = threadIdx.x; i < 4 * a.K; i += blockDim.x) {
-    const int which = i / a.K, idx = i - which * a.K;
-    lds_cf[4 * idx + which] = cf[i];
+  if constexpr (sizeof(S) == 4) {
+    jerk_points_mm<LB>(a,
+                       reinterpret_cast<const float*>(a.cf) +
+                           size_t(__builtin_amdgcn_readfirstlane(sys)) * 2 * mm_offset(a.lmax + 1, a.nmax),
+                       ub, ue, blockDim.x);
+  } else {
+    const Dual<S>* __restrict__ cf = reinterpret_cast<const Dual<S>*>(a.cf) + size_t(sys) * 4 * a.K;
+    Dual<S>* lds_cf = reinterpret_cast<Dual<S>*>(jerk_lds);
+    for (int i = threadIdx.x; i < 4 * a.K; i += blockDim.x) {
+      const int which = i / a.K, idx = i - which * a.K;
+      lds_cf[4 * idx + which] = cf[i];
+    }
+    __syncthreads();
+    jerk_points_f64<LB, LdsPtr<Dual<S>>, true>(a, (LdsPtr<Dual<S>>)(lds_cf), ub, ue, blockDim.x);
   }
-  __syncthreads();
-  const LdsPtr<Dual<S>> src = (LdsPtr<Dual<S>>)(lds_cf);
-  for (int64_t i = ub + threadIdx.x; i < ue; i += blockDim.x)
-    jerk_point<S, LB, LdsPtr<Dual<S>>, true>(a, src, i);
 }
 
 namespace {
@@ -188,9 +243,9 @@ struct JerkBatch {
 template <typename S, int LBV>
 void launch_jerk_kernel(const JerkArgs& a, int grid, const JerkBatch* bi, hipStream_t st) {
   if (bi) {
-    // 4 K Dual values of LDS (at the largest cutoffs 79 KiB in FP32, 158 KiB in FP64;
-    // failures surface at the launch)
-    const size_t lds = size_t(4) * a.K * sizeof(Dual<S>);
+    // FP64: 4 K Dual values of LDS (at the largest cutoffs 158 KiB; failures surface at the
+    // launch)
+    const size_t lds = sizeof(S) == 8 ? size_t(4) * a.K * sizeof(Dual<S>) : 0;
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(scf_jerk_batched_kernel<S, LBV>),
                         hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     hipLaunchKernelGGL((scf_jerk_batched_kernel<S, LBV>), dim3(grid), dim3(256), lds, st, a, bi->offsets,
@@ -219,14 +274,12 @@ int launch_jerk_lb(const JerkArgs& a, int grid, const JerkBatch* bi, hipStream_t
 
 int launch_jerk_prep(const double* A, const double* B, const double* Ad, const double* Bd, int nmax,
                      int lmax, int nsys, int prec, void* cf, hipStream_t st) {
+  if (prec != ETICS_FP64)
+    return launch_force_prep_mm(A, B, Ad, Bd, nmax, lmax, nsys, kBasisHO, reinterpret_cast<float*>(cf), st);
   const int K = coeff_count(nmax, lmax);
   const int pb = int((int64_t(nsys) * K + 255) / 256);
-  if (prec == ETICS_FP64)
-    hipLaunchKernelGGL(scf_jerk_prep_kernel<double>, dim3(pb), dim3(256), 0, st, A, B, Ad, Bd, nmax, lmax,
+  hipLaunchKernelGGL(scf_jerk_prep_kernel<double>, dim3(pb), dim3(256), 0, st, A, B, Ad, Bd, nmax, lmax,
                        nsys, reinterpret_cast<Dual<double>*>(cf));
-  else
-    hipLaunchKernelGGL(scf_jerk_prep_kernel<float>, dim3(pb), dim3(256), 0, st, A, B, Ad, Bd, nmax, lmax,
-                       nsys, reinterpret_cast<Dual<float>*>(cf));
   return hip_fail(hipGetLastError(), "scf_jerk_prep_kernel launch");
 }
 
