@@ -419,9 +419,10 @@ def mex_extra(torch, np, etics, workloads, stream, reps, ex):
         etics.etics_set_timing_events(None, None)
         torch.cuda.synchronize()
         ms = e0.elapsed_time(e1) / reps
-        # algorithmic bytes: x, y, z, m in and pot, a out (64 B) plus 8 radix passes over
-        # an 8-byte key and a 4-byte index, read and written (8 x 24 B)
-        mex_bytes = n * (64 + 8 * 24)
+        # algorithmic bytes: x, y, z, m in and pot, a out (64 B) plus the sample sort: the
+        # 8-byte key written, read for the bucket counts (1 B out) and for the scatter into
+        # the buckets (9 B in, 12 B out), and the sort of each bucket (12 B in, 4 B out)
+        mex_bytes = n * (64 + 8 + 9 + 21 + 16)
         ex[f"mex_{name}"] = {"workload": "mex_plummer_hernquist_n1e6_l10", "ms_per_call": ms,
                              "particles_per_s": n / (ms * 1e-3), "synthesis_kernel_ms": kt.mean_ms(),
                              "algorithmic_bytes": mex_bytes,
