@@ -67,8 +67,8 @@ constexpr int kBucketKPT = 11;                      // keys of each,
 constexpr int kBucketTile = kBucketThreads * kBucketKPT;  // and the keys that LDS holds at once
 // Where the line between the sorts lies, us a MEX call at lmax 10 (radix sort alone / as
 // chosen here): the rank count is O(n^2), but one kernel: 143 / 54 at 1000 particles, 164 /
-// 77 at 8000 (94 at 9000 with the sample sort); sample sort 181 / 111 at 10^5, 490 / 397 at
-// 10^6.  A bucket holds 16 samples' worth of keys; up to kSampleMost one that outgrows the
+// 77 at 8000 (94 at 9000 with the sample sort); sample sort 184 / 115 at 10^5 (FP64), 500 /
+// 405 at 10^6 (mixed).  A bucket holds 16 samples' worth of keys; up to kSampleMost one that outgrows the
 // LDS has to be 2.75 times the mean (of random inputs, one in 10^4 has such a bucket).
 constexpr int64_t kRankMost = 8192;
 constexpr int64_t kSampleMost = int64_t(kBuckets) * 4096;
@@ -490,16 +490,20 @@ __global__ __launch_bounds__(kBucketThreads) void bucket_sort_kernel(uint64_t* k
     }
     __syncthreads();
   };
-  // ranks of the keys of a tile of tn keys (rounds of 64 a wavefront) in their wavefront
+  // ranks of the keys of a tile (rounds of 64 a wavefront; left = keys from this lane's
+  // first on) in their wavefront, each with its digit above (16 bits).  With a digit and a
+  // position in registers of their own for every key, 140 registers went to scratch (33 MB
+  // written a call): 37 -> 31 us at n = 10^6, 16.5 -> 14.5 at 10^5
   uint64_t k[kBucketKPT];
   uint32_t v[kBucketKPT], rank[kBucketKPT];
-  auto rank_tile = [&](int tn, int rounds, int shift) __attribute__((always_inline)) {
+  static_assert(kBucketTile <= 1 << 16, "a rank and its digit share 32 bits");
+  auto rank_tile = [&](int left, int rounds, int shift) __attribute__((always_inline)) {
     for (int i = t; i < kWaves * 256; i += kBucketThreads) (&cnt[0][0])[i] = 0;
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kBucketKPT; ++j) {
       if (j < rounds) {
-        const bool valid = (w * rounds + j) * 64 + lane < tn;
+        const bool valid = 64 * j < left;
         const uint32_t d = uint32_t(k[j] >> shift) & 0xffu;
         const uint64_t same = same_digit_lanes(d, valid);
         const uint32_t below = uint32_t(__popcll(same & lt_mask));
@@ -508,7 +512,8 @@ __global__ __launch_bounds__(kBucketThreads) void bucket_sort_kernel(uint64_t* k
           r = cnt[w][d];
           if (below == 0) cnt[w][d] = r + uint32_t(__popcll(same));
         }
-        rank[j] = r + below;
+        rank[j] = (d << 16) + r + below;
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
     __syncthreads();
@@ -517,21 +522,21 @@ __global__ __launch_bounds__(kBucketThreads) void bucket_sort_kernel(uint64_t* k
   if (m <= kBucketTile) {
     const int tn = int(m);
     const int rounds = (tn + kBucketThreads - 1) / kBucketThreads;
+    const int first = w * rounds * 64 + lane, left = tn - first;
 #pragma unroll
     for (int j = 0; j < kBucketKPT; ++j) {
-      const int i = (w * rounds + j) * 64 + lane;
       if (j < rounds) {
-        k[j] = i < tn ? k0[i] - kmin : 0ull;
-        v[j] = i < tn ? v0[i] : 0u;
+        k[j] = 64 * j < left ? k0[first + 64 * j] - kmin : 0ull;
+        v[j] = 64 * j < left ? v0[first + 64 * j] : 0u;
       }
     }
     auto pass = [&](int shift) __attribute__((always_inline)) {
-      rank_tile(tn, rounds, shift);
+      rank_tile(left, rounds, shift);
       starts();
 #pragma unroll
       for (int j = 0; j < kBucketKPT; ++j) {
-        if (j < rounds && (w * rounds + j) * 64 + lane < tn) {
-          const uint32_t pos = cnt[w][uint32_t(k[j] >> shift) & 0xffu] + rank[j];
+        if (j < rounds && 64 * j < left) {
+          const uint32_t pos = cnt[w][rank[j] >> 16] + (rank[j] & 0xffffu);
           if (pos < uint32_t(kBucketTile)) {  // always true; keeps a logic error inside the tile
             sk[pos] = k[j];
             sv[pos] = v[j];
@@ -541,10 +546,9 @@ __global__ __launch_bounds__(kBucketThreads) void bucket_sort_kernel(uint64_t* k
       __syncthreads();
 #pragma unroll
       for (int j = 0; j < kBucketKPT; ++j) {
-        const int i = (w * rounds + j) * 64 + lane;
-        if (j < rounds && i < tn) {
-          k[j] = sk[i];
-          v[j] = sv[i];
+        if (j < rounds && 64 * j < left) {
+          k[j] = sk[first + 64 * j];
+          v[j] = sv[first + 64 * j];
         }
       }
       __syncthreads();
@@ -562,8 +566,8 @@ __global__ __launch_bounds__(kBucketThreads) void bucket_sort_kernel(uint64_t* k
       bool too_long = false;
       static_for<kBucketKPT>([&](auto jc) {  // (the loops inside keep a for from unrolling)
         constexpr int j = decltype(jc)::value;
-        const int i = (w * rounds + j) * 64 + lane;
-        if (j < rounds && i < tn) {
+        const int i = first + 64 * j;
+        if (j < rounds && 64 * j < left) {
           const uint64_t mine = k[j], run = mine >> lo;
           int s = i, before = 0, e = i + 1;
           while (s > 0 && i - s < kRunMost && (sk[s - 1] >> lo) == run) {
@@ -582,19 +586,15 @@ __global__ __launch_bounds__(kBucketThreads) void bucket_sort_kernel(uint64_t* k
       __syncthreads();
       if (base[0] == 0) {
 #pragma unroll
-        for (int j = 0; j < kBucketKPT; ++j) {
-          const int i = (w * rounds + j) * 64 + lane;
-          if (j < rounds && i < tn) perm[rank[j]] = v[j];
-        }
+        for (int j = 0; j < kBucketKPT; ++j)
+          if (j < rounds && 64 * j < left) perm[rank[j]] = v[j];
         return;
       }
     }
     for (int shift = 0; shift < top; shift += 8) pass(shift);
 #pragma unroll
-    for (int j = 0; j < kBucketKPT; ++j) {
-      const int i = (w * rounds + j) * 64 + lane;
-      if (j < rounds && i < tn) perm[i] = v[j];
-    }
+    for (int j = 0; j < kBucketKPT; ++j)
+      if (j < rounds && 64 * j < left) perm[first + 64 * j] = v[j];
     return;
   }
 
@@ -617,13 +617,13 @@ __global__ __launch_bounds__(kBucketThreads) void bucket_sort_kernel(uint64_t* k
     __syncthreads();
     for (int64_t t0 = 0; t0 < m; t0 += kBucketTile) {
       const int tn = int(m - t0 < kBucketTile ? m - t0 : kBucketTile);
+      const int first = w * kBucketKPT * 64 + lane, left = tn - first;
 #pragma unroll
       for (int j = 0; j < kBucketKPT; ++j) {
-        const int i = (w * kBucketKPT + j) * 64 + lane;
-        k[j] = i < tn ? ka[t0 + i] - kmin : 0ull;
-        v[j] = i < tn ? va[t0 + i] : 0u;
+        k[j] = 64 * j < left ? ka[t0 + first + 64 * j] - kmin : 0ull;
+        v[j] = 64 * j < left ? va[t0 + first + 64 * j] : 0u;
       }
-      rank_tile(tn, kBucketKPT, shift);
+      rank_tile(left, kBucketKPT, shift);
       // positions within the digit: the wavefronts' counts before this one's
       uint32_t own = 0;
       if (t < 256) {
@@ -637,8 +637,8 @@ __global__ __launch_bounds__(kBucketThreads) void bucket_sort_kernel(uint64_t* k
       __syncthreads();
 #pragma unroll
       for (int j = 0; j < kBucketKPT; ++j) {
-        if ((w * kBucketKPT + j) * 64 + lane < tn) {
-          const uint32_t pos = cnt[w][uint32_t(k[j] >> shift) & 0xffu] + rank[j];
+        if (64 * j < left) {
+          const uint32_t pos = cnt[w][rank[j] >> 16] + (rank[j] & 0xffffu);
           if (int64_t(pos) < m) {  // always true; keeps a logic error inside the bucket
             kb[pos] = k[j] + kmin;
             vb[pos] = v[j];
