@@ -67,7 +67,7 @@ constexpr int kBucketKPT = 11;                      // keys of each,
 constexpr int kBucketTile = kBucketThreads * kBucketKPT;  // and the keys that LDS holds at once
 // Where the line between the sorts lies, us a MEX call at lmax 10 (radix sort alone / as
 // chosen here): the rank count is O(n^2), but one kernel: 143 / 54 at 1000 particles, 164 /
-// 77 at 8000 (94 at 9000 with the sample sort); sample sort 184 / 115 at 10^5 (FP64), 500 /
+// 77 at 8000 (94 at 9000 with the sample sort); sample sort 184 / 113 at 10^5 (FP64), 500 /
 // 405 at 10^6 (mixed).  A bucket holds 16 samples' worth of keys; up to kSampleMost one that outgrows the
 // LDS has to be 2.75 times the mean (of random inputs, one in 10^4 has such a bucket).
 constexpr int64_t kRankMost = 8192;
@@ -243,7 +243,9 @@ __global__ __launch_bounds__(kSortThreads) void radix_count_kernel(const uint64_
 }
 
 // The same for the bucket of every key (digit[i], 0 .. 255): the last splitter, from 1 on,
-// that is not above (key, index), found by bisection in LDS.
+// that is not above (key, index), found by bisection in LDS, a thread's keys side by side so
+// that their reads overlap (one key after another: 7.6 us at n = 10^5, now 5.6; at 10^6 10.1,
+// now 9.2).
 __global__ __launch_bounds__(kSortThreads) void bucket_count_kernel(
     const uint64_t* __restrict__ key, int64_t n, int ntiles, const uint64_t* __restrict__ skey,
     const uint32_t* __restrict__ sidx, uint8_t* __restrict__ digit, uint32_t* __restrict__ counts) {
@@ -251,24 +253,29 @@ __global__ __launch_bounds__(kSortThreads) void bucket_count_kernel(
   __shared__ uint64_t bk[kBuckets];
   __shared__ uint32_t bi[kBuckets];
   const int t = threadIdx.x;
+  const int64_t t0 = int64_t(blockIdx.x) * kSortTile;
+  const int tn = int(n - t0 < kSortTile ? n - t0 : kSortTile);
+  uint64_t k[kSortKPT];
+#pragma unroll
+  for (int j = 0; j < kSortKPT; ++j) k[j] = j * kSortThreads + t < tn ? key[t0 + j * kSortThreads + t] : 0ull;
   h[t] = 0;
   bk[t] = skey[t];
   bi[t] = sidx[t];
   __syncthreads();
-  const int64_t t0 = int64_t(blockIdx.x) * kSortTile;
-  const int tn = int(n - t0 < kSortTile ? n - t0 : kSortTile);
+  uint32_t b[kSortKPT] = {};
+#pragma unroll
+  for (uint32_t step = kBuckets / 2; step > 0; step /= 2)
+#pragma unroll
+    for (int j = 0; j < kSortKPT; ++j) {
+      const uint32_t c = b[j] + step;
+      if (!pair_less(k[j], uint32_t(t0 + j * kSortThreads + t), bk[c], bi[c])) b[j] = c;
+    }
 #pragma unroll
   for (int j = 0; j < kSortKPT; ++j) {
     const int i = j * kSortThreads + t;
     if (i < tn) {
-      const uint64_t k = key[t0 + i];
-      const uint32_t id = uint32_t(t0 + i);
-      uint32_t b = 0;
-#pragma unroll
-      for (uint32_t step = kBuckets / 2; step > 0; step /= 2)
-        if (!pair_less(k, id, bk[b + step], bi[b + step])) b += step;
-      digit[t0 + i] = uint8_t(b);
-      atomicAdd(&h[b], 1u);
+      digit[t0 + i] = uint8_t(b[j]);
+      atomicAdd(&h[b[j]], 1u);
     }
   }
   __syncthreads();
