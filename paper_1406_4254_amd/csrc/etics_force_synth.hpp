@@ -255,32 +255,35 @@ struct RadialMM {
   static_assert(ACC || sizeof(T) == 4, "a Dual potential alone is not instantiated");
   using Quad = typename QuadOf<T>::type;
   static constexpr bool kDual = sizeof(T) == 8;
-  // The coefficients through a buffer descriptor: its base and the position are scalar,
-  // so a lane keeps one offset register for every load, and the lanes past the values of
-  // a short run read the following ones, or zero past the array's end.
-  __amdgpu_buffer_rsrc_t cf;
-  int nmax, lane4;        // lane4: the lane's byte offset
-  int der;                // Dual: position of the derivatives' array
-  int pos;                // start of the current l
+  // The coefficients through buffer descriptors, one for each array.  A lane's position is
+  // the load's vector offset, with a constant added in the instruction: both are compared
+  // with the array's size, so the lanes past the values of a short run read the following
+  // ones, and what lies past the array's end (the last loads of the last l, not used) is
+  // zero and not read.  (A scalar offset would not be compared.)
+  __amdgpu_buffer_rsrc_t cf, cd;  // cd: Dual, the derivatives
+  int nmax;
+  int at;                 // byte offset of this lane's value at the start of the current l
   // this lane's coefficients: order 0; the next two pairs of orders (U, V and W, X)
   T a0, x0, y0, x1, y1;
 
+  static __device__ __forceinline__ __amdgpu_buffer_rsrc_t array(const float* p, int values) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, 4 * values, 0x00020000);
+  }
   // cfp: the prepared coefficients of one system, the same pointer in every lane
   __device__ __forceinline__ RadialMM(const float* cfp, int nmax_, int lmax_)
-      : cf(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(cfp), 0,
-                                             (kDual ? 8 : 4) * mm_offset(lmax_ + 1, nmax_), 0x00020000)),
-        nmax(nmax_), lane4(4 * int(threadIdx.x & 63)), der(mm_offset(lmax_ + 1, nmax_)), pos(0), a0(T(0.f)),
-        x0(T(0.f)), y0(T(0.f)), x1(T(0.f)), y1(T(0.f)) {}
+      : cf(array(cfp, mm_offset(lmax_ + 1, nmax_))),
+        cd(array(kDual ? cfp + mm_offset(lmax_ + 1, nmax_) : cfp, mm_offset(lmax_ + 1, nmax_))), nmax(nmax_), at(0),
+        a0(T(0.f)), x0(T(0.f)), y0(T(0.f)), x1(T(0.f)), y1(T(0.f)) {}
 
-  // this lane's value at position pos + off
-  __device__ __forceinline__ float load1(int at) const {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(cf, lane4, 4 * at, 0));
+  // this lane's value `off` values on from the start of the current l
+  __device__ __forceinline__ float load1(__amdgpu_buffer_rsrc_t r, int off) const {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, at + 4 * off, 0, 0));
   }
   __device__ __forceinline__ T load(int off) const {
     if constexpr (kDual)
-      return T(load1(pos + off), load1(pos + off + der));
+      return T(load1(cf, off), load1(cd, off));
     else
-      return load1(pos + off);
+      return load1(cf, off);
   }
   // one register holds a pair's U, V and W, X quads if they are at most 16
   template <int l>
@@ -289,14 +292,16 @@ struct RadialMM {
   // pair J of the orders of l (past the last pair: other values, not used)
   template <int l, int J>
   __device__ __forceinline__ void load_pair(T& x, T& y) const {
-    constexpr int at = 4 * mm_quads(l) * (1 + 4 * J);
-    x = load(at);
-    if constexpr (ACC && !one_reg<l>()) y = load(at + 8 * mm_quads(l));
+    constexpr int off = 4 * mm_quads(l) * (1 + 4 * J);
+    x = load(off);
+    if constexpr (ACC && !one_reg<l>()) y = load(off + 8 * mm_quads(l));
   }
   // the first loads of l, issued before the previous l's angular synthesis
   template <int l>
   __device__ __forceinline__ void start() {
-    if constexpr (l == 0) pos = 0;
+    if constexpr (l == 0) at = 4 * int(threadIdx.x & 63);
+    // opaque, so that no load's address is kept over the loop on points
+    asm volatile("" : "+v"(at));
     a0 = load(0);
     load_pair<l, 0>(x0, y0);
     load_pair<l, 1>(x1, y1);
@@ -371,7 +376,7 @@ struct RadialMM {
       }
     };
     pairs(pairs, std::integral_constant<int, 0>{});
-    pos += 4 * NQ * (1 + 4 * npairs);
+    at += 16 * NQ * (1 + 4 * npairs);
 #pragma unroll
     for (int m = 0; m <= l; ++m) {
       U[m] = QuadOf<T>::get(uv[m / 4], m % 4);

@@ -1,0 +1,60 @@
+"""What the compiler made of the FP32 force and jerk kernels, read from the library built
+here: properties that a run cannot show, or shows only as lost time."""
+import os
+import re
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIBPATH = os.path.join(ROOT, "paper_1406_4254_amd", "libetics.so")
+LLVM = os.environ.get("ETICS_LLVM", "/opt/rocm/llvm/bin")
+
+pytestmark = pytest.mark.skipif(not os.path.exists(os.path.join(LLVM, "llvm-objdump")),
+                                reason="needs ROCm's llvm-objdump")
+
+
+@pytest.fixture(scope="module")
+def code_objects(tmp_path_factory):
+    """The gfx950 code objects of the library, extracted into a folder of their own."""
+    if not os.path.exists(LIBPATH):
+        from paper_1406_4254_amd import build
+        build.build()
+    d = tmp_path_factory.mktemp("code")
+    os.symlink(LIBPATH, d / "lib.so")
+    subprocess.run([os.path.join(LLVM, "llvm-objdump"), "--offloading", "lib.so"], cwd=d, check=True,
+                   capture_output=True)
+    found = sorted(str(p) for p in d.iterdir() if p.name.endswith("gfx950"))
+    assert found
+    return found
+
+
+def kernels(path, pattern):
+    """Names of a code object's kernels that match."""
+    out = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "-s", "--wide", path], check=True,
+                         capture_output=True, text=True).stdout
+    names = {line.split()[-1] for line in out.splitlines() if " FUNC " in line}
+    return sorted(n for n in names if re.search(pattern, n))
+
+
+def test_coefficient_loads_are_range_checked(code_objects):
+    """The FP32 force and jerk kernels ask for coefficients past the last ones and leave the
+    answer to the range check of their buffer descriptor, which compares the vector and the
+    instruction's offset with the array's size: no load may carry its position in the scalar
+    offset, which is not compared."""
+    loads = 0
+    for path in code_objects:
+        names = kernels(path, r"scf_(force|jerk)(_batched)?_kernelIf")
+        if not names:
+            continue
+        out = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", "--mcpu=gfx950",
+                              "--disassemble-symbols=" + ",".join(names), path], check=True, capture_output=True,
+                             text=True).stdout
+        for line in out.splitlines():
+            m = re.match(r"\s+buffer_load_\w+ v\S+, v\d+, s\[\d+:\d+\], (\S+)(.*)", line)
+            if not m:
+                assert "buffer_load" not in line, line
+                continue
+            loads += 1
+            assert m.group(1) == "0" and "offen" in m.group(2), line
+    assert loads > 1000
