@@ -245,8 +245,8 @@ struct QuadOf<Dual<float>> {
   static __device__ __forceinline__ Dual<float> get(const type& q, int i) { return {q.v[i], q.d[i]}; }
 };
 __host__ __device__ constexpr int mm_quads(int l) { return slot_pad(l, 4) / 4; }
-// pairs of orders from order 1 on (at least one, so the first needs no branch)
-__host__ __device__ constexpr int mm_pairs(int nmax) { return nmax < 1 ? 1 : (nmax + 1) / 2; }
+// pairs of orders from order 1 on
+__host__ __device__ constexpr int mm_pairs(int nmax) { return (nmax + 1) / 2; }
 // floats of the l's before l, and of the whole array (l = lmax + 1)
 __host__ __device__ constexpr int mm_offset(int l, int nmax) { return zoff(l, 4) * (1 + 4 * mm_pairs(nmax)); }
 
@@ -375,7 +375,12 @@ struct RadialMM {
         if (J + 1 < npairs) self(self, std::integral_constant<int, J + 1>{});
       }
     };
-    pairs(pairs, std::integral_constant<int, 0>{});
+    // (no pair at nmax = 0: xi is NaN where r overflows, and times a zero coefficient it
+    // would reach the monopole's potential there)
+    if (npairs > 0)
+      pairs(pairs, std::integral_constant<int, 0>{});
+    else if constexpr (ACC)
+      static_for<NQ>([&](auto qc) { wx[decltype(qc)::value] = zero; });
     at += 16 * NQ * (1 + 4 * npairs);
 #pragma unroll
     for (int m = 0; m <= l; ++m) {
