@@ -72,34 +72,33 @@ size_t jerk_prep_bytes(int nmax, int lmax, int prec) {
 }
 
 // ---------------------------------------------------------------- jerk pass
-// What the jerk pass does with a particle's a and j:
-//   kOut:     write them to the output arrays;
+// What the jerk pass of a Hermite step does with a particle's a and j:
 //   kStart:   store them as the state's a, j and predict the first step;
 //   kStep:    correct the state with them, store them, predict the next step;
 //   kLast:    correct the state with them and store them.
-enum HermiteMode { kOut = 0, kStart = 1, kStep = 2, kLast = 3 };
+enum HermiteMode { kStart = 1, kStep = 2, kLast = 3 };
 
 struct JerkArgs {
   const double *x, *y, *z, *vx, *vy, *vz;  // field points and their velocities
   int64_t n;
   const void* cf;                          // prepared Dual coefficients
-  double *ax, *ay, *az, *jx, *jy, *jz;     // kOut: outputs; otherwise the state's a and j
-  // Hermite state (modes other than kOut): positions and velocities corrected in place,
-  // and the predicted ones (the field points of the next pass)
+  double *ax, *ay, *az, *jx, *jy, *jz;     // single system: outputs; Hermite: the state's a and j
+  // Hermite state: positions and velocities corrected in place, and the predicted ones (the
+  // field points of the next pass)
   double *sx, *sy, *sz, *svx, *svy, *svz;
   double *px, *py, *pz, *pvx, *pvy, *pvz;
   int K, nmax, lmax, mode;
   double dt;
 };
 
-// point i's acceleration and jerk o go where the mode says
-template <typename S>
+// point i's acceleration and jerk o: to the outputs, or (HERMITE) where the mode says
+template <typename S, bool HERMITE>
 __device__ __forceinline__ void jerk_store(const JerkArgs& a, int64_t i, const ForceOut<Dual<S>>& o) {
   const double g[3] = {double(o.gx.v), double(o.gy.v), double(o.gz.v)};
   const double jk[3] = {double(o.gx.d), double(o.gy.d), double(o.gz.d)};
   double* A[3] = {a.ax, a.ay, a.az};
   double* J[3] = {a.jx, a.jy, a.jz};
-  if (a.mode == kOut) {
+  if constexpr (!HERMITE) {
     for (int c = 0; c < 3; ++c) {
       A[c][i] = g[c];
       J[c][i] = jk[c];
@@ -141,12 +140,12 @@ __device__ __forceinline__ void jerk_store(const JerkArgs& a, int64_t i, const F
 
 // The points [i0, i1), one per lane.  FP64: FMAs on coefficients read through the
 // constant address space ([4][K]) or from LDS (LdsPtr, QUAD: [K][4]).
-template <int LB, typename CP, bool QUAD>
+template <int LB, bool HERMITE, typename CP, bool QUAD>
 __device__ __forceinline__ void jerk_points_f64(const JerkArgs& a, CP cf, int64_t i0, int64_t i1, int64_t stride) {
   for (int64_t i = i0 + threadIdx.x; i < i1; i += stride) {
     const auto s = sph_dual<double, kBasisHO>(a.x[i], a.y[i], a.z[i], a.vx[i], a.vy[i], a.vz[i]);
     RadialVec<Dual<double>, true, kBasisHO, CP, QUAD> rad{cf, a.K, a.nmax, a.lmax};
-    jerk_store<double>(a, i, synth_point<Dual<double>, LB, true, kBasisHO>(s, rad, a.lmax));
+    jerk_store<double, HERMITE>(a, i, synth_point<Dual<double>, LB, true, kBasisHO>(s, rad, a.lmax));
   }
 }
 // FP32: the radial sums on the matrix cores, which need every lane: the loop is uniform over
@@ -154,7 +153,7 @@ __device__ __forceinline__ void jerk_points_f64(const JerkArgs& a, CP cf, int64_
 // a wavefront issues 3050 VALU and matrix instructions a point instead of 4600, which shows
 // only once the memory traffic of the Hermite step (290 bytes a particle) is asked for in
 // time: a lane's next point and the state to correct are read together, before any write.
-// 256 systems, (8, 6), 5 steps: 10.78 -> 10.02 ms (10.87 with the matrix cores alone).
+// 256 systems, (8, 6), 4 steps: 8.96 -> 8.45 ms.
 template <int LB>
 __device__ __forceinline__ void jerk_points_mm(const JerkArgs& a, const float* cf, int64_t i0, int64_t i1,
                                                int64_t stride) {
@@ -178,25 +177,47 @@ __device__ __forceinline__ void jerk_points_mm(const JerkArgs& a, const float* c
     // before the stores: loads and stores are waited for in order
     load(i + stride);
     rad.template start<0>();
-    if (i < i1) jerk_store<float>(a, i, o);
+    if (i < i1) jerk_store<float, true>(a, i, o);
   }
 }
 
+// A single system's points, one per lane and no loop over them, as in scf_force_f64_kernel:
+// in a loop every array's address stayed in registers over the synthesis (48 of them, most of
+// them in scratch).  N = 10^6, vector FMAs / matrix cores in a loop / here, us a call: (4, 4)
+// 59 / 64 / 54, (8, 6) 142 / 165 / 116, (10, 10) 425 / 372 / 276, (20, 14) 2440 / 2470 / 936.
+template <int LB>
+__device__ __forceinline__ void jerk_point_mm(const JerkArgs& a, int64_t i) {
+  RadialMM<Dual<float>, true, kBasisHO> rad(reinterpret_cast<const float*>(a.cf), a.nmax, a.lmax);
+  rad.template start<0>();
+  const bool valid = i < a.n;
+  const auto s = sph_dual<float, kBasisHO>(valid ? a.x[i] : 0.0, valid ? a.y[i] : 0.0, valid ? a.z[i] : 0.0,
+                                           valid ? a.vx[i] : 0.0, valid ? a.vy[i] : 0.0, valid ? a.vz[i] : 0.0);
+  const auto o = synth_point<Dual<float>, LB, true, kBasisHO>(s, rad, a.lmax);
+  if (valid) jerk_store<float, false>(a, i, o);
+}
+
+// Wavefronts a SIMD (the second launch bound), FP32: as many as the registers allow without
+// scratch, or with little of it where that measured faster.  Single system, N = 10^6, us a
+// call: (8, 6) 3 (52 bytes of scratch a lane) / 2 (none) 119 / 124; (10, 10) 2 / 1 276 / 376;
+// (12, 12) 2 (128 bytes) / 1 (none) 414 / 548; (20, 14) 2 (460 bytes) / 1 (none) 870 / 939, but
+// 78 / 65 at 10^4.  Batched, Hermite steps, ms: (8, 6) 3 (120 bytes) / 2 (none) 8.52 / 8.43;
+// (12, 12) 2 (416 bytes) / 1 (none) 16.3 / 16.7; (20, 14) 2 (604 bytes) / 1 (none) 22.3 / 20.4.
 template <typename S, int LB>
-__global__ __launch_bounds__(256, sizeof(S) == 8 ? 1 : LB <= 6 ? 3 : 2) void scf_jerk_kernel(const JerkArgs a) {
-  const int64_t i0 = int64_t(blockIdx.x) * blockDim.x, stride = int64_t(gridDim.x) * blockDim.x;
+__global__ __launch_bounds__(256, sizeof(S) == 8 ? 1 : LB <= 6 ? 3 : LB <= 12 ? 2 : 1) void scf_jerk_kernel(const JerkArgs a) {
+  const int64_t i0 = int64_t(blockIdx.x) * blockDim.x;
   if constexpr (sizeof(S) == 4)
-    jerk_points_mm<LB>(a, reinterpret_cast<const float*>(a.cf), i0, a.n, stride);
+    jerk_point_mm<LB>(a, i0 + threadIdx.x);
   else
-    jerk_points_f64<LB, ConstPtr<Dual<double>>, false>(
-        a, ConstPtr<Dual<double>>(reinterpret_cast<const Dual<double>*>(a.cf)), i0, a.n, stride);
+    jerk_points_f64<LB, false, ConstPtr<Dual<double>>, false>(
+        a, ConstPtr<Dual<double>>(reinterpret_cast<const Dual<double>*>(a.cf)), i0, a.n,
+        int64_t(gridDim.x) * blockDim.x);
 }
 
 // batched systems: `split` workgroups per unit of `unit` particles of one system, as the
 // batched force kernel; FP64: the workgroup first copies its system's prepared coefficients
 // to LDS as [K][4] and reads them as broadcast VGPR operands
 template <typename S, int LB>
-__global__ __launch_bounds__(256, sizeof(S) == 8 ? 1 : LB <= 6 ? 3 : 2) void scf_jerk_batched_kernel(const JerkArgs a,
+__global__ __launch_bounds__(256, sizeof(S) == 8 ? 1 : LB <= 4 ? 3 : LB <= 12 ? 2 : 1) void scf_jerk_batched_kernel(const JerkArgs a,
                                                                const int64_t* __restrict__ offsets,
                                                                const int* __restrict__ ustart,
                                                                const int* __restrict__ usys, int nsys,
@@ -227,7 +248,7 @@ __global__ __launch_bounds__(256, sizeof(S) == 8 ? 1 : LB <= 6 ? 3 : 2) void scf
       lds_cf[4 * idx + which] = cf[i];
     }
     __syncthreads();
-    jerk_points_f64<LB, LdsPtr<Dual<S>>, true>(a, (LdsPtr<Dual<S>>)(lds_cf), ub, ue, blockDim.x);
+    jerk_points_f64<LB, true, LdsPtr<Dual<S>>, true>(a, (LdsPtr<Dual<S>>)(lds_cf), ub, ue, blockDim.x);
   }
 }
 
@@ -250,8 +271,19 @@ void launch_jerk_kernel(const JerkArgs& a, int grid, const JerkBatch* bi, hipStr
                         hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     hipLaunchKernelGGL((scf_jerk_batched_kernel<S, LBV>), dim3(grid), dim3(256), lds, st, a, bi->offsets,
                        bi->ustart, bi->usys, bi->nsys, bi->unit, bi->split);
-  } else
+  } else if constexpr (sizeof(S) == 8) {
     hipLaunchKernelGGL((scf_jerk_kernel<S, LBV>), dim3(grid), dim3(256), 0, st, a);
+  } else {
+    // a grid holds less than 2^32 threads
+    constexpr int64_t kMost = int64_t(1) << 30;
+    for (int64_t at = 0; at < a.n; at += kMost) {
+      JerkArgs b = a;
+      b.n = a.n - at < kMost ? a.n - at : kMost;
+      for (const double** p : {&b.x, &b.y, &b.z, &b.vx, &b.vy, &b.vz}) *p += at;
+      for (double** p : {&b.ax, &b.ay, &b.az, &b.jx, &b.jy, &b.jz}) *p += at;
+      hipLaunchKernelGGL((scf_jerk_kernel<S, LBV>), dim3(unsigned((b.n + 255) / 256)), dim3(256), 0, st, b);
+    }
+  }
 }
 
 template <typename S>
@@ -314,7 +346,6 @@ int launch_scf_jerk(const double* x, const double* y, const double* z, const dou
   a.K = coeff_count(nmax, lmax);
   a.nmax = nmax;
   a.lmax = lmax;
-  a.mode = kOut;
   int64_t grid = (n + 255) / 256;
   if (grid > 65536) grid = 65536;
   return launch_jerk_any(a, prec, int(grid), nullptr, st);

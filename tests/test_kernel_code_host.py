@@ -51,10 +51,32 @@ def test_coefficient_loads_are_range_checked(code_objects):
                               "--disassemble-symbols=" + ",".join(names), path], check=True, capture_output=True,
                              text=True).stdout
         for line in out.splitlines():
-            m = re.match(r"\s+buffer_load_\w+ v\S+, v\d+, s\[\d+:\d+\], (\S+)(.*)", line)
+            m = re.match(r"\s+buffer_load_\w+ [av]\S+, v\d+, s\[\d+:\d+\], (\S+)(.*)", line)
             if not m:
                 assert "buffer_load" not in line, line
                 continue
             loads += 1
             assert m.group(1) == "0" and "offen" in m.group(2), line
     assert loads > 1000
+
+
+# bytes of scratch a lane that the FP32 jerk kernels may use, by lmax bucket (else none): where
+# a wavefront more on each SIMD measured faster than the registers it costs
+SCRATCH = {"scf_jerk_kernel": {6: 64, 10: 32, 12: 128}, "scf_jerk_batched_kernel": {10: 64, 12: 448}}
+
+
+def test_jerk_kernels_keep_their_registers(code_objects):
+    """The FP32 jerk kernels once held most of their values in scratch (1300 bytes a lane at the
+    largest cutoffs), which made the single-system call slower than vector FMAs."""
+    seen = 0
+    for path in code_objects:
+        notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", path], check=True, capture_output=True,
+                               text=True).stdout
+        for block in re.split(r"\n  - \.", notes):
+            m = re.search(r"\.name:\s+_ZN5etics\d+(scf_jerk_kernel|scf_jerk_batched_kernel)IfLi(\d+)E", block)
+            if not m:
+                continue
+            seen += 1
+            scratch = int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", block).group(1))
+            assert scratch <= SCRATCH[m.group(1)].get(int(m.group(2)), 0), m.group(0)
+    assert seen == 14
