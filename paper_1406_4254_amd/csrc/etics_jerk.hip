@@ -138,16 +138,32 @@ __device__ __forceinline__ void jerk_store(const JerkArgs& a, int64_t i, const F
   }
 }
 
-// The points [i0, i1), one per lane.  FP64: FMAs on coefficients read through the
-// constant address space ([4][K]) or from LDS (LdsPtr, QUAD: [K][4]).
-template <int LB, bool HERMITE, typename CP, bool QUAD>
-__device__ __forceinline__ void jerk_points_f64(const JerkArgs& a, CP cf, int64_t i0, int64_t i1, int64_t stride) {
-  for (int64_t i = i0 + threadIdx.x; i < i1; i += stride) {
-    const auto s = sph_dual<double, kBasisHO>(a.x[i], a.y[i], a.z[i], a.vx[i], a.vy[i], a.vz[i]);
-    RadialVec<Dual<double>, true, kBasisHO, CP, QUAD> rad{cf, a.K, a.nmax, a.lmax};
-    jerk_store<double, HERMITE>(a, i, synth_point<Dual<double>, LB, true, kBasisHO>(s, rad, a.lmax));
-  }
+// FP64: point i, FMAs on coefficients read through the constant address space ([4][K]) or
+// from LDS (QUAD: [K][4]).  No kernel loops over points here: the compiler moves the FP64
+// constants out of such a loop, and the registers for them are not there (290 of them went to
+// vector lanes at (8, 6)).  A single system, N = 10^6, with a loop / here, us a call: (8, 6) 413 /
+// 395, (12, 12) 3670 / 2450, (20, 14) 8380 / 5570.
+template <int LB, bool HERMITE, bool QUAD, typename CP>
+__device__ __forceinline__ void jerk_point_f64(const JerkArgs& a, CP cf, int64_t i) {
+  const auto s = sph_dual<double, kBasisHO>(a.x[i], a.y[i], a.z[i], a.vx[i], a.vy[i], a.vz[i]);
+  RadialVec<Dual<double>, true, kBasisHO, CP, QUAD> rad{cf, a.K, a.nmax, a.lmax};
+  jerk_store<double, HERMITE>(a, i, synth_point<Dual<double>, LB, true, kBasisHO>(s, rad, a.lmax));
 }
+// one system's prepared coefficients, [4][K], to the workgroup's LDS as [K][4]
+__device__ __forceinline__ void jerk_coeffs_to_lds(const Dual<double>* cf, int K, Dual<double>* lds) {
+  for (int i = threadIdx.x; i < 4 * K; i += blockDim.x) {
+    const int which = i / K, idx = i - which * K;
+    lds[4 * idx + which] = cf[i];
+  }
+  __syncthreads();
+}
+// Where a single system's FP64 coefficients are read from: LDS from lmax bucket 12 on, where
+// the scalar loads' latency bounds the one wavefront a SIMD holds ((20, 14): 501 / 344 us a call
+// at N = 10^4, 8.40 / 5.57 ms at 10^6); below, the LDS reads do at large N ((10, 10): 1.27 / 1.49
+// ms at 10^6).
+template <typename S, int LB>
+constexpr bool kJerkLds = sizeof(S) == 8 && LB > 10;
+
 // FP32: the radial sums on the matrix cores, which need every lane: the loop is uniform over
 // the workgroup and a lane past the end computes a point at rest at the origin.  At (8, 6)
 // a wavefront issues 3050 VALU and matrix instructions a point instead of 4600, which shows
@@ -181,10 +197,10 @@ __device__ __forceinline__ void jerk_points_mm(const JerkArgs& a, const float* c
   }
 }
 
-// A single system's points, one per lane and no loop over them, as in scf_force_f64_kernel:
-// in a loop every array's address stayed in registers over the synthesis (48 of them, most of
-// them in scratch).  N = 10^6, vector FMAs / matrix cores in a loop / here, us a call: (4, 4)
-// 59 / 64 / 54, (8, 6) 142 / 165 / 116, (10, 10) 425 / 372 / 276, (20, 14) 2440 / 2470 / 936.
+// A single system's points, one per lane and no loop over them: in a loop every array's address
+// stayed in registers over the synthesis (48 of them, most of them in scratch).  N = 10^6, vector
+// FMAs / matrix cores in a loop / here, us a call: (4, 4) 59 / 64 / 54, (8, 6) 142 / 165 / 116,
+// (10, 10) 425 / 372 / 276, (20, 14) 2440 / 2470 / 936.
 template <int LB>
 __device__ __forceinline__ void jerk_point_mm(const JerkArgs& a, int64_t i) {
   RadialMM<Dual<float>, true, kBasisHO> rad(reinterpret_cast<const float*>(a.cf), a.nmax, a.lmax);
@@ -204,18 +220,26 @@ __device__ __forceinline__ void jerk_point_mm(const JerkArgs& a, int64_t i) {
 // (12, 12) 2 (416 bytes) / 1 (none) 16.3 / 16.7; (20, 14) 2 (604 bytes) / 1 (none) 22.3 / 20.4.
 template <typename S, int LB>
 __global__ __launch_bounds__(256, sizeof(S) == 8 ? 1 : LB <= 6 ? 3 : LB <= 12 ? 2 : 1) void scf_jerk_kernel(const JerkArgs a) {
-  const int64_t i0 = int64_t(blockIdx.x) * blockDim.x;
-  if constexpr (sizeof(S) == 4)
-    jerk_point_mm<LB>(a, i0 + threadIdx.x);
-  else
-    jerk_points_f64<LB, false, ConstPtr<Dual<double>>, false>(
-        a, ConstPtr<Dual<double>>(reinterpret_cast<const Dual<double>*>(a.cf)), i0, a.n,
-        int64_t(gridDim.x) * blockDim.x);
+  extern __shared__ __align__(16) unsigned char jerk_lds[];
+  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if constexpr (sizeof(S) == 4) {
+    jerk_point_mm<LB>(a, i);
+  } else if constexpr (kJerkLds<S, LB>) {
+    Dual<S>* lds_cf = reinterpret_cast<Dual<S>*>(jerk_lds);
+    jerk_coeffs_to_lds(reinterpret_cast<const Dual<S>*>(a.cf), a.K, lds_cf);
+    if (i < a.n) jerk_point_f64<LB, false, true>(a, (LdsPtr<Dual<S>>)(lds_cf), i);
+  } else {
+    if (i < a.n)
+      jerk_point_f64<LB, false, false>(a, ConstPtr<Dual<S>>(reinterpret_cast<const Dual<S>*>(a.cf)), i);
+  }
 }
 
-// batched systems: `split` workgroups per unit of `unit` particles of one system, as the
-// batched force kernel; FP64: the workgroup first copies its system's prepared coefficients
-// to LDS as [K][4] and reads them as broadcast VGPR operands
+// batched systems: `split` (times gridDim.y) workgroups per unit of `unit` particles of one
+// system, as the batched force kernel; FP64: the workgroup first copies its system's prepared
+// coefficients to LDS as [K][4] and reads them as broadcast VGPR operands, and its part has at
+// most one particle for each lane, so that there is no loop out of which the constants are moved
+// (to vector lanes).  With a loop / here, 4 Hermite steps, ms: 128 systems (8, 6) 9.13 / 8.49,
+// (20, 14) 78.6 / 73.4; 16 systems of 1000 (8, 6) 1.44 / 0.97.
 template <typename S, int LB>
 __global__ __launch_bounds__(256, sizeof(S) == 8 ? 1 : LB <= 4 ? 3 : LB <= 12 ? 2 : 1) void scf_jerk_batched_kernel(const JerkArgs a,
                                                                const int64_t* __restrict__ offsets,
@@ -224,13 +248,14 @@ __global__ __launch_bounds__(256, sizeof(S) == 8 ? 1 : LB <= 4 ? 3 : LB <= 12 ? 
                                                                int unit, int split) {
   extern __shared__ __align__(16) unsigned char jerk_lds[];
   const int u = blockIdx.x / split;
-  const int part = blockIdx.x % split;
+  const int part = blockIdx.x % split + split * blockIdx.y;
   if (u >= ustart[nsys]) return;
   const int sys = usys[u];
   int64_t b = offsets[sys], e = offsets[sys + 1];
   b = b < 0 ? 0 : (b > a.n ? a.n : b);
   e = e < b ? b : (e > a.n ? a.n : e);
-  const int64_t kPart = (unit + split - 1) / split;
+  const int parts = split * gridDim.y;
+  const int64_t kPart = (unit + parts - 1) / parts;
   const int64_t u0 = b + int64_t(u - ustart[sys]) * unit;
   const int64_t ue0 = u0 + unit < e ? u0 + unit : e;
   const int64_t ub = u0 + part * kPart < ue0 ? u0 + part * kPart : ue0;
@@ -241,14 +266,11 @@ __global__ __launch_bounds__(256, sizeof(S) == 8 ? 1 : LB <= 4 ? 3 : LB <= 12 ? 
                            size_t(__builtin_amdgcn_readfirstlane(sys)) * 2 * mm_offset(a.lmax + 1, a.nmax),
                        ub, ue, blockDim.x);
   } else {
-    const Dual<S>* __restrict__ cf = reinterpret_cast<const Dual<S>*>(a.cf) + size_t(sys) * 4 * a.K;
+    if (ub >= ue) return;
     Dual<S>* lds_cf = reinterpret_cast<Dual<S>*>(jerk_lds);
-    for (int i = threadIdx.x; i < 4 * a.K; i += blockDim.x) {
-      const int which = i / a.K, idx = i - which * a.K;
-      lds_cf[4 * idx + which] = cf[i];
-    }
-    __syncthreads();
-    jerk_points_f64<LB, true, LdsPtr<Dual<S>>, true>(a, (LdsPtr<Dual<S>>)(lds_cf), ub, ue, blockDim.x);
+    jerk_coeffs_to_lds(reinterpret_cast<const Dual<S>*>(a.cf) + size_t(sys) * 4 * a.K, a.K, lds_cf);
+    const int64_t i = ub + threadIdx.x;
+    if (i < ue) jerk_point_f64<LB, true, true>(a, (LdsPtr<Dual<S>>)(lds_cf), i);
   }
 }
 
@@ -263,26 +285,28 @@ struct JerkBatch {
 
 template <typename S, int LBV>
 void launch_jerk_kernel(const JerkArgs& a, int grid, const JerkBatch* bi, hipStream_t st) {
+  // FP64 from LDS: 4 K Dual values (at the largest cutoffs 158 KiB; failures surface at the
+  // launch)
+  const size_t lds = sizeof(S) == 8 && (bi || kJerkLds<S, LBV>) ? size_t(4) * a.K * sizeof(Dual<S>) : 0;
+  auto allow = [&](const void* kfn) {
+    if (lds) (void)hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  };
   if (bi) {
-    // FP64: 4 K Dual values of LDS (at the largest cutoffs 158 KiB; failures surface at the
-    // launch)
-    const size_t lds = sizeof(S) == 8 ? size_t(4) * a.K * sizeof(Dual<S>) : 0;
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(scf_jerk_batched_kernel<S, LBV>),
-                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    hipLaunchKernelGGL((scf_jerk_batched_kernel<S, LBV>), dim3(grid), dim3(256), lds, st, a, bi->offsets,
+    allow(reinterpret_cast<const void*>(scf_jerk_batched_kernel<S, LBV>));
+    const int rows = sizeof(S) == 8 ? (bi->unit + 256 * bi->split - 1) / (256 * bi->split) : 1;
+    hipLaunchKernelGGL((scf_jerk_batched_kernel<S, LBV>), dim3(grid, rows), dim3(256), lds, st, a, bi->offsets,
                        bi->ustart, bi->usys, bi->nsys, bi->unit, bi->split);
-  } else if constexpr (sizeof(S) == 8) {
-    hipLaunchKernelGGL((scf_jerk_kernel<S, LBV>), dim3(grid), dim3(256), 0, st, a);
-  } else {
-    // a grid holds less than 2^32 threads
-    constexpr int64_t kMost = int64_t(1) << 30;
-    for (int64_t at = 0; at < a.n; at += kMost) {
-      JerkArgs b = a;
-      b.n = a.n - at < kMost ? a.n - at : kMost;
-      for (const double** p : {&b.x, &b.y, &b.z, &b.vx, &b.vy, &b.vz}) *p += at;
-      for (double** p : {&b.ax, &b.ay, &b.az, &b.jx, &b.jy, &b.jz}) *p += at;
-      hipLaunchKernelGGL((scf_jerk_kernel<S, LBV>), dim3(unsigned((b.n + 255) / 256)), dim3(256), 0, st, b);
-    }
+    return;
+  }
+  allow(reinterpret_cast<const void*>(scf_jerk_kernel<S, LBV>));
+  // a grid holds less than 2^32 threads
+  constexpr int64_t kMost = int64_t(1) << 30;
+  for (int64_t at = 0; at < a.n; at += kMost) {
+    JerkArgs b = a;
+    b.n = a.n - at < kMost ? a.n - at : kMost;
+    for (const double** p : {&b.x, &b.y, &b.z, &b.vx, &b.vy, &b.vz}) *p += at;
+    for (double** p : {&b.ax, &b.ay, &b.az, &b.jx, &b.jy, &b.jz}) *p += at;
+    hipLaunchKernelGGL((scf_jerk_kernel<S, LBV>), dim3(unsigned((b.n + 255) / 256)), dim3(256), lds, st, b);
   }
 }
 
@@ -346,9 +370,7 @@ int launch_scf_jerk(const double* x, const double* y, const double* z, const dou
   a.K = coeff_count(nmax, lmax);
   a.nmax = nmax;
   a.lmax = lmax;
-  int64_t grid = (n + 255) / 256;
-  if (grid > 65536) grid = 65536;
-  return launch_jerk_any(a, prec, int(grid), nullptr, st);
+  return launch_jerk_any(a, prec, 0, nullptr, st);
 }
 
 // ---------------------------------------------------------------- Hermite driver

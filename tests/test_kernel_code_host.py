@@ -65,18 +65,31 @@ def test_coefficient_loads_are_range_checked(code_objects):
 SCRATCH = {"scf_jerk_kernel": {6: 64, 10: 32, 12: 128}, "scf_jerk_batched_kernel": {10: 64, 12: 448}}
 
 
-def test_jerk_kernels_keep_their_registers(code_objects):
-    """The FP32 jerk kernels once held most of their values in scratch (1300 bytes a lane at the
-    largest cutoffs), which made the single-system call slower than vector FMAs."""
-    seen = 0
+def kernel_notes(code_objects, pattern):
+    """The compiler's notes on every kernel whose name matches, with the match."""
     for path in code_objects:
         notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", path], check=True, capture_output=True,
                                text=True).stdout
         for block in re.split(r"\n  - \.", notes):
-            m = re.search(r"\.name:\s+_ZN5etics\d+(scf_jerk_kernel|scf_jerk_batched_kernel)IfLi(\d+)E", block)
-            if not m:
-                continue
-            seen += 1
-            scratch = int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", block).group(1))
-            assert scratch <= SCRATCH[m.group(1)].get(int(m.group(2)), 0), m.group(0)
+            m = re.search(r"\.name:\s+_ZN5etics\d+" + pattern, block)
+            if m:
+                yield m, {k: int(v) for k, v in re.findall(r"\.(\w+):\s+(\d+)\n", block)}
+
+
+def test_jerk_kernels_keep_their_registers(code_objects):
+    """The FP32 jerk kernels once held most of their values in scratch (1300 bytes a lane at the
+    largest cutoffs), which made the single-system call slower than vector FMAs."""
+    seen = 0
+    for m, note in kernel_notes(code_objects, r"(scf_jerk_kernel|scf_jerk_batched_kernel)IfLi(\d+)E"):
+        seen += 1
+        assert note["private_segment_fixed_size"] <= SCRATCH[m.group(1)].get(int(m.group(2)), 0), m.group(0)
     assert seen == 14
+
+
+def test_fp64_jerk_keeps_its_constants(code_objects):
+    """The FP64 jerk kernels have no loop over points out of which their constants could be moved
+    (they went to vector lanes, up to 1100 of them)."""
+    found = list(kernel_notes(code_objects, r"scf_jerk(_batched)?_kernelIdLi\d+E"))
+    assert len(found) == 14
+    for m, note in found:
+        assert note["sgpr_spill_count"] == 0, m.group(0)
