@@ -229,8 +229,11 @@ __global__ __launch_bounds__(256, 2) void scf_force_f64_kernel(const ForceArgs a
 // the coefficient kernel's units gives the force pass more workgroups.  FP64: the
 // system's prepared coefficients are copied to LDS as [K][2] first, as in
 // scf_force_f64_kernel; FP32: as in scf_force_kernel.
+// The potential alone at lmax > 10 in FP64 asks for one wavefront a SIMD: held to the registers
+// of two, the compiler keeps fewer LDS reads in flight.  Two / one, us a call: 128 systems (9, 12)
+// 286 / 248, (20, 14) 780 / 676; 16 systems of 1000 (9, 12) 90 / 72, (20, 14) 243 / 195.
 template <typename T, int LB, bool ACC>
-__global__ __launch_bounds__(256, sizeof(T) == 8 ? (LB <= 6 ? 3 : 2) : LB <= 10 ? 4 : 3) void scf_force_batched_kernel(const ForceArgs a,
+__global__ __launch_bounds__(256, sizeof(T) == 8 ? (LB <= 6 ? 3 : LB > 10 && !ACC ? 1 : 2) : LB <= 10 ? 4 : 3) void scf_force_batched_kernel(const ForceArgs a,
                                                                 const int64_t* __restrict__ offsets,
                                                                 const int* __restrict__ ustart,
                                                                 const int* __restrict__ usys,
