@@ -291,7 +291,7 @@ struct CoeffWG {
     T* Zp = Z + pidx * SPZ;
     T xi;
     if (maxm_w >= 0) {
-      const Sph<T> s = sph<T, BASIS>(xd, yd, zd);
+      const Sph<T> s = sph<T, BASIS, false>(xd, yd, zd);
       xi = s.xi;
       angular_jobs(s, md, Zp, Zp);
     } else {  // radial jobs only: xi alone
@@ -314,7 +314,7 @@ struct CoeffWG {
     T* Zder = Zval + SPZ;
     Dual<T> xi;
     if (maxm_w >= 0) {
-      const Sph<Dual<T>> s = sph_dual<T, BASIS>(xd, yd, zd, vxd, vyd, vzd);
+      const Sph<Dual<T>> s = sph_dual<T, BASIS, false>(xd, yd, zd, vxd, vyd, vzd);
       xi = s.xi;
       angular_jobs(s, md, Zval, Zder);
     } else {

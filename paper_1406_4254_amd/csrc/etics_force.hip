@@ -168,7 +168,7 @@ __device__ __forceinline__ void force_points_mm(const ForceArgs& a, const float*
   for (; i0 < i1; i0 += stride) {
     const int64_t i = i0 + threadIdx.x;
     if constexpr (!NEXT) load(i);
-    const Sph<float> s = sph<float, BASIS>(x, y, z);
+    const Sph<float> s = sph<float, BASIS, true>(x, y, z);
     const ForceOut<float> o = synth_point<float, LB, ACC, BASIS>(s, rad, a.lmax);
     if constexpr (NEXT) load(i + stride);
     // before the stores: loads and stores are waited for in order
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(256, LB <= 10 ? 4 : 3) void scf_force_kernel(const 
 // coefficients are scalar operands: 119 -> 96 us at N = 10^6, (10, 10).
 template <bool ACC, int BASIS, int LB, typename Radial>
 __device__ __forceinline__ void force_point_f64(const ForceArgs& a, Radial rad, int64_t i) {
-  const Sph<double> s = sph<double, BASIS>(a.x[i], a.y[i], a.z[i]);
+  const Sph<double> s = sph<double, BASIS, true>(a.x[i], a.y[i], a.z[i]);
   const ForceOut<double> o = synth_point<double, LB, ACC, BASIS>(s, rad, a.lmax);
   force_store<double, ACC>(a, i, o.pot, o.gx, o.gy, o.gz);
 }

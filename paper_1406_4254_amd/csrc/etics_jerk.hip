@@ -145,7 +145,7 @@ __device__ __forceinline__ void jerk_store(const JerkArgs& a, int64_t i, const F
 // 395, (12, 12) 3670 / 2450, (20, 14) 8380 / 5570.
 template <int LB, bool HERMITE, bool QUAD, typename CP>
 __device__ __forceinline__ void jerk_point_f64(const JerkArgs& a, CP cf, int64_t i) {
-  const auto s = sph_dual<double, kBasisHO>(a.x[i], a.y[i], a.z[i], a.vx[i], a.vy[i], a.vz[i]);
+  const auto s = sph_dual<double, kBasisHO, true>(a.x[i], a.y[i], a.z[i], a.vx[i], a.vy[i], a.vz[i]);
   RadialVec<Dual<double>, true, kBasisHO, CP, QUAD> rad{cf, a.K, a.nmax, a.lmax};
   jerk_store<double, HERMITE>(a, i, synth_point<Dual<double>, LB, true, kBasisHO>(s, rad, a.lmax));
 }
@@ -188,7 +188,7 @@ __device__ __forceinline__ void jerk_points_mm(const JerkArgs& a, const float* c
   load(i0 + threadIdx.x);
   for (; i0 < i1; i0 += stride) {
     const int64_t i = i0 + threadIdx.x;
-    const auto s = sph_dual<float, kBasisHO>(x, y, z, vx, vy, vz);
+    const auto s = sph_dual<float, kBasisHO, true>(x, y, z, vx, vy, vz);
     const auto o = synth_point<Dual<float>, LB, true, kBasisHO>(s, rad, a.lmax);
     // before the stores: loads and stores are waited for in order
     load(i + stride);
@@ -206,7 +206,7 @@ __device__ __forceinline__ void jerk_point_mm(const JerkArgs& a, int64_t i) {
   RadialMM<Dual<float>, true, kBasisHO> rad(reinterpret_cast<const float*>(a.cf), a.nmax, a.lmax);
   rad.template start<0>();
   const bool valid = i < a.n;
-  const auto s = sph_dual<float, kBasisHO>(valid ? a.x[i] : 0.0, valid ? a.y[i] : 0.0, valid ? a.z[i] : 0.0,
+  const auto s = sph_dual<float, kBasisHO, true>(valid ? a.x[i] : 0.0, valid ? a.y[i] : 0.0, valid ? a.z[i] : 0.0,
                                            valid ? a.vx[i] : 0.0, valid ? a.vy[i] : 0.0, valid ? a.vz[i] : 0.0);
   const auto o = synth_point<Dual<float>, LB, true, kBasisHO>(s, rad, a.lmax);
   if (valid) jerk_store<float, false>(a, i, o);
