@@ -42,8 +42,10 @@ __global__ __launch_bounds__(64 * WAVES) void direct_force_kernel(
   constexpr int kSlices = 4 * WAVES;
   constexpr int NV = (POT ? 1 : 0) + (ACC ? 3 : 0);
   __shared__ double sums[NV][kSlices][NT * kTargetLanes];
+  const int64_t group = int64_t(blockIdx.y) * gridDim.x + blockIdx.x;
+  if (group * (NT * kTargetLanes) >= n) return;
   const int tl = threadIdx.x % kTargetLanes, slice = threadIdx.x / kTargetLanes;
-  const int64_t t0 = int64_t(blockIdx.x) * (NT * kTargetLanes) + tl;
+  const int64_t t0 = group * (NT * kTargetLanes) + tl;
   double px[NT], py[NT], pz[NT], P[NT] = {}, gx[NT] = {}, gy[NT] = {}, gz[NT] = {};
 #pragma unroll
   for (int k = 0; k < NT; ++k) {
@@ -96,7 +98,7 @@ __global__ __launch_bounds__(64 * WAVES) void direct_force_kernel(
   __syncthreads();
   for (int o = threadIdx.x; o < NV * NT * kTargetLanes; o += 64 * WAVES) {
     const int v = o / (NT * kTargetLanes), e = o % (NT * kTargetLanes);
-    const int64_t i = int64_t(blockIdx.x) * (NT * kTargetLanes) + e;
+    const int64_t i = group * (NT * kTargetLanes) + e;
     if (i >= n) continue;
     double s = sums[v][0][e];
     for (int q = 1; q < kSlices; ++q) s += sums[v][q][e];
@@ -109,7 +111,10 @@ namespace {
 template <int NT, int WAVES>
 void launch_direct(const double* x, const double* y, const double* z, const double* m, int64_t n,
                    int outputs, double* pot, double* ax, double* ay, double* az, hipStream_t st) {
-  const dim3 grid(unsigned((n + NT * kTargetLanes - 1) / (NT * kTargetLanes))), block(64 * WAVES);
+  // rows of workgroups: a row holds less than 2^32 threads (one row of all n < 2^31 targets would not)
+  const int64_t groups = (n + NT * kTargetLanes - 1) / (NT * kTargetLanes);
+  const int64_t row = groups < 4096 ? groups : 4096;
+  const dim3 grid(unsigned(row), unsigned((groups + row - 1) / row)), block(64 * WAVES);
   if (outputs == ETICS_POT)
     hipLaunchKernelGGL((direct_force_kernel<NT, WAVES, true, false>), grid, block, 0, st, x, y, z, m, n, pot, ax, ay, az);
   else if (outputs == ETICS_ACC)
