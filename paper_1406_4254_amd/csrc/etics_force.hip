@@ -66,8 +66,8 @@ __global__ __launch_bounds__(256) void scf_force_prep_kernel(const double* __res
   c[K + k] = su * b;
 }
 
-// FP32: the quad layout of RadialMM, one thread per value; with Ad, Bd (the jerk) each
-// system's coefficients are followed by their time derivatives
+// FP32: the quad layout of RadialMM, one value per thread and trip; with Ad, Bd (the jerk)
+// each system's coefficients are followed by their time derivatives
 __global__ __launch_bounds__(256) void scf_force_prep_mm_kernel(const double* __restrict__ A,
                                                                const double* __restrict__ B,
                                                                const double* __restrict__ Ad,
@@ -75,33 +75,34 @@ __global__ __launch_bounds__(256) void scf_force_prep_mm_kernel(const double* __
                                                                int nmax, int lmax, int nsys, int basis,
                                                                float* __restrict__ cf) {
   const int Q = mm_offset(lmax + 1, nmax);
-  const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (g >= int64_t(nsys) * Q) return;
-  const int sys = int(g / Q);
-  int e = int(g - int64_t(sys) * Q);
-  const int rep = 1 + 4 * mm_pairs(nmax);  // runs of padded slots per l
-  int l = 0;
-  while (e >= slot_pad(l, 4) * rep) {
-    e -= slot_pad(l, 4) * rep;
-    ++l;
+  for (int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; g < int64_t(nsys) * Q;
+       g += int64_t(gridDim.x) * blockDim.x) {
+    const int sys = int(g / Q);
+    int e = int(g - int64_t(sys) * Q);
+    const int rep = 1 + 4 * mm_pairs(nmax);  // runs of padded slots per l
+    int l = 0;
+    while (e >= slot_pad(l, 4) * rep) {
+      e -= slot_pad(l, 4) * rep;
+      ++l;
+    }
+    const int P = slot_pad(l, 4);
+    const int run = e / P, slot = e - run * P;
+    // run 0: order 0 of U, V; then per pair j: U, V of 1+2j, of 2+2j, W, X of 1+2j, of 2+2j
+    const int n = run == 0 ? 0 : 1 + 2 * ((run - 1) / 4) + ((run - 1) & 1);
+    const bool deriv = run > 0 && (((run - 1) >> 1) & 1);
+    float v = 0.f, d = 0.f;
+    if (n <= nmax && slot <= 2 * l) {
+      const int m = slot <= l ? slot : slot - l;
+      const int K = (nmax + 1) * (lmax + 1) * (lmax + 2) / 2;
+      const int64_t k = int64_t(sys) * K + n * ((lmax + 1) * (lmax + 2) / 2) + l * (l + 1) / 2 + m;
+      const double scale = deriv ? g_force_scales.sw[basis][n][l] : g_force_scales.su[basis][n][l];
+      v = float(scale * (slot <= l ? A[k] : B[k]));
+      if (Ad) d = float(scale * (slot <= l ? Ad[k] : Bd[k]));
+    }
+    float* const c = cf + size_t(sys) * (Ad ? 2 * Q : Q);
+    c[g - int64_t(sys) * Q] = v;
+    if (Ad) c[Q + (g - int64_t(sys) * Q)] = d;
   }
-  const int P = slot_pad(l, 4);
-  const int run = e / P, slot = e - run * P;
-  // run 0: order 0 of U, V; then per pair j: U, V of 1+2j, of 2+2j, W, X of 1+2j, of 2+2j
-  const int n = run == 0 ? 0 : 1 + 2 * ((run - 1) / 4) + ((run - 1) & 1);
-  const bool deriv = run > 0 && (((run - 1) >> 1) & 1);
-  float v = 0.f, d = 0.f;
-  if (n <= nmax && slot <= 2 * l) {
-    const int m = slot <= l ? slot : slot - l;
-    const int K = (nmax + 1) * (lmax + 1) * (lmax + 2) / 2;
-    const int64_t k = int64_t(sys) * K + n * ((lmax + 1) * (lmax + 2) / 2) + l * (l + 1) / 2 + m;
-    const double scale = deriv ? g_force_scales.sw[basis][n][l] : g_force_scales.su[basis][n][l];
-    v = float(scale * (slot <= l ? A[k] : B[k]));
-    if (Ad) d = float(scale * (slot <= l ? Ad[k] : Bd[k]));
-  }
-  float* const c = cf + size_t(sys) * (Ad ? 2 * Q : Q);
-  c[g - int64_t(sys) * Q] = v;
-  if (Ad) c[Q + (g - int64_t(sys) * Q)] = d;
 }
 
 // ------------------------------------------------------------------------ force
@@ -265,9 +266,10 @@ __global__ __launch_bounds__(256, sizeof(T) == 8 ? (LB <= 6 ? 3 : LB > 10 && !AC
 
 int launch_force_prep_mm(const double* A, const double* B, const double* Ad, const double* Bd, int nmax, int lmax,
                          int nsys, int basis, float* cf, hipStream_t st) {
-  const int64_t values = int64_t(nsys) * mm_offset(lmax + 1, nmax);
-  hipLaunchKernelGGL(scf_force_prep_mm_kernel, dim3(unsigned((values + 255) / 256)), dim3(256), 0, st, A, B, Ad, Bd,
-                     nmax, lmax, nsys, basis, cf);
+  // (many systems' values would be 2^32 threads, more than a grid holds)
+  const int64_t values = int64_t(nsys) * mm_offset(lmax + 1, nmax), blocks = (values + 255) / 256;
+  hipLaunchKernelGGL(scf_force_prep_mm_kernel, dim3(unsigned(blocks < 65536 ? blocks : 65536)), dim3(256), 0, st, A, B,
+                     Ad, Bd, nmax, lmax, nsys, basis, cf);
   return hip_fail(hipGetLastError(), "scf_force_prep_mm_kernel launch");
 }
 
@@ -365,13 +367,11 @@ int launch_force_lb(int lb, const ForceArgs& a, int basis, int grid, const Batch
 
 int launch_prep(const double* A, const double* B, int nmax, int lmax, int nsys, int prec, int basis,
                 void* ws, hipStream_t st) {
-  const int64_t values = int64_t(nsys) * (prec == ETICS_FP64 ? coeff_count(nmax, lmax) : mm_offset(lmax + 1, nmax));
-  const int pb = int((values + 255) / 256);
-  if (prec == ETICS_FP64)
-    hipLaunchKernelGGL(scf_force_prep_kernel, dim3(pb), dim3(256), 0, st, A, B, nmax, lmax, nsys, basis,
-                       reinterpret_cast<double*>(ws));
-  else
+  if (prec != ETICS_FP64)
     return launch_force_prep_mm(A, B, nullptr, nullptr, nmax, lmax, nsys, basis, reinterpret_cast<float*>(ws), st);
+  const int pb = int((int64_t(nsys) * coeff_count(nmax, lmax) + 255) / 256);
+  hipLaunchKernelGGL(scf_force_prep_kernel, dim3(pb), dim3(256), 0, st, A, B, nmax, lmax, nsys, basis,
+                     reinterpret_cast<double*>(ws));
   return hip_fail(hipGetLastError(), "scf_force_prep_kernel launch");
 }
 
