@@ -110,8 +110,10 @@ BatchedLayout batched_layout(int64_t ntotal, int nsys, int nmax, int lmax, int p
   const size_t nn = size_t(ntotal > 0 ? ntotal : 1);
   L.off_ustart = take(size_t(nsys + 1) * 4);
   L.off_usys = take(size_t(mu) * 4);
-  L.off_partials = take(size_t(mu) * 2 * K * 8);
-  L.off_prep = take(size_t(nsys) * force_prep_bytes(nmax, lmax, prec));
+  const PrepRegion r = prep_region(o, mu, nsys, K, size_t(4) * K, force_prep_bytes(nmax, lmax, prec), prec);
+  L.off_partials = r.off_partials;
+  L.off_prep = r.off_prep;
+  o = r.end;
   L.off_A = take(size_t(nsys) * K * 8);
   L.off_B = take(size_t(nsys) * K * 8);
   L.off_acc = take(3 * nn * 8);

@@ -139,6 +139,22 @@ int launch_scf_force_batched(const CoeffPlan& plan, const double* x, const doubl
                              const double* B, int outputs, double* pot, double* ax, double* ay,
                              double* az, void* prep, hipStream_t st, const LfUpdate* lf = nullptr);
 
+// Where a batched workspace holds its units' partial sums and, once those are summed, the
+// coefficients prepared for the force or jerk pass: one after the other, with room for `values`
+// plain numbers of compute precision per system.  The FP32 layout for the matrix cores pads some
+// cutoffs past that ((8, 6) by 8%); it begins inside the partial sums then, which are dead by the
+// time it is written, so that a workspace of the unpadded size is enough.
+struct PrepRegion {
+  size_t off_partials, off_prep, end;
+};
+inline PrepRegion prep_region(size_t at, int units, int nsys, int K, size_t values, size_t prep_bytes, int prec) {
+  const size_t partials = align_up(size_t(units) * 2 * K * 8, 256), prep = align_up(nsys * prep_bytes, 256);
+  const size_t plain = align_up(nsys * values * (prec == ETICS_FP64 ? 8 : 4), 256);
+  const size_t after = partials + (prep < plain ? prep : plain);
+  const size_t end = at + (after > prep ? after : prep);
+  return {at, end - prep, end};
+}
+
 struct BatchedLayout {
   size_t off_ustart, off_usys, off_partials, off_prep, off_A, off_B, off_acc, total;
   int max_units;

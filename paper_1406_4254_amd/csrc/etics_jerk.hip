@@ -382,8 +382,8 @@ struct HermiteLayout {
   bool ok;
 };
 
-// workspace: unit tables, partial vectors (shared by both coefficient passes), the
-// prepared Dual coefficients, A, B, dA/dt, dB/dt per system, and per particle a, j
+// workspace: unit tables, partial vectors (shared by both coefficient passes) and the
+// prepared Dual coefficients (prep_region), A, B, dA/dt, dB/dt per system, and per particle a, j
 // and the predicted position and velocity (12 doubles)
 HermiteLayout hermite_layout(int64_t ntotal, int nsys, int nmax, int lmax, int prec) {
   HermiteLayout L{};
@@ -400,8 +400,10 @@ HermiteLayout hermite_layout(int64_t ntotal, int nsys, int nmax, int lmax, int p
   const size_t nn = size_t(ntotal > 0 ? ntotal : 1);
   L.off_ustart = take(size_t(nsys + 1) * 4);
   L.off_usys = take(size_t(mu) * 4);
-  L.off_partials = take(size_t(mu) * 2 * K * 8);
-  L.off_prep = take(size_t(nsys) * jerk_prep_bytes(nmax, lmax, prec));
+  const PrepRegion r = prep_region(o, mu, nsys, K, size_t(8) * K, jerk_prep_bytes(nmax, lmax, prec), prec);
+  L.off_partials = r.off_partials;
+  L.off_prep = r.off_prep;
+  o = r.end;
   L.off_A = take(size_t(nsys) * K * 8);
   L.off_B = take(size_t(nsys) * K * 8);
   L.off_Ad = take(size_t(nsys) * K * 8);
