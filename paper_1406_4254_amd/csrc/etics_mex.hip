@@ -100,6 +100,13 @@ __device__ __forceinline__ uint32_t block_excl_scan_u32(uint32_t v, uint32_t* ws
 }
 
 // ------------------------------------------------------------------ keys
+// (x x + y y) + z z with every operation rounded: without the pragma the compiler fuses them
+// (__dmul_rn and __dadd_rn are plain products and sums to it)
+__device__ __forceinline__ uint64_t mex_key(double x, double y, double z) {
+#pragma clang fp contract(off)
+  const double xx = x * x, yy = y * y, zz = z * z;
+  return __double_as_longlong((xx + yy) + zz);
+}
 __global__ __launch_bounds__(256) void mex_keys_kernel(const double* __restrict__ x,
                                                        const double* __restrict__ y,
                                                        const double* __restrict__ z, int64_t n,
@@ -107,16 +114,8 @@ __global__ __launch_bounds__(256) void mex_keys_kernel(const double* __restrict_
                                                        uint32_t* __restrict__ idx) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const double xx = __dmul_rn(x[i], x[i]);
-  const double yy = __dmul_rn(y[i], y[i]);
-  const double zz = __dmul_rn(z[i], z[i]);
-  const double k = __dadd_rn(__dadd_rn(xx, yy), zz);
-  key[i] = __double_as_longlong(k);
+  key[i] = mex_key(x[i], y[i], z[i]);
   if (idx) idx[i] = uint32_t(i);
-}
-
-__device__ __forceinline__ uint64_t mex_key(double x, double y, double z) {
-  return __double_as_longlong(__dadd_rn(__dadd_rn(__dmul_rn(x, x), __dmul_rn(y, y)), __dmul_rn(z, z)));
 }
 
 // ------------------------------------------------------------------ rank by counting
