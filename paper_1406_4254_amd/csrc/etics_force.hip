@@ -109,7 +109,7 @@ __global__ __launch_bounds__(256) void scf_force_prep_mm_kernel(const double* __
 struct ForceArgs {
   const double *x, *y, *z;
   int64_t n;
-  const void* cf;  // prepared coefficients: quad layout (FP32) or 4K (FP64)
+  const void* cf;  // prepared coefficients: quad layout (FP32) or 2K (FP64)
   double *pot, *ax, *ay, *az;
   int K, nmax, lmax;
   int want_pot;
@@ -286,13 +286,6 @@ struct BatchInfo {
   int nsys, unit, split;
 };
 
-// the whole 160 KiB of a CU may be requested as dynamic LDS (the largest cutoffs' FP64
-// coefficients take 80 KiB); hipFuncSetAttribute once per kernel (failures surface at
-// the launch)
-void set_lds_limit(const void* kfn) {
-  (void)hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-}
-
 // FP64, one point per lane.  Potential only: scalar coefficient operands for many points
 // and lmax > 6, where the LDS reads bound the pass; elsewhere the scalar loads' latency
 // shows.  LDS against scalar operands, us a call: (10, 10) 26 / 33 at 10^5 points, 43 / 45
@@ -300,9 +293,8 @@ void set_lds_limit(const void* kfn) {
 constexpr int64_t kScalarPoints = 400000;
 template <bool ACC, int LBV, int BASIS>
 void launch_force_f64(const ForceArgs& a, hipStream_t st) {
-  const size_t lds = size_t(2) * a.K * sizeof(double);
+  const size_t lds = size_t(2) * a.K * sizeof(double);  // at most 40 KiB
   const bool scalar = !ACC && LBV > 6 && a.n >= kScalarPoints;
-  if (!scalar) set_lds_limit(reinterpret_cast<const void*>(scf_force_f64_kernel<LBV, ACC, BASIS, true>));
   // a grid holds less than 2^32 threads
   constexpr int64_t kMost = int64_t(1) << 30;
   for (int64_t at = 0; at < a.n; at += kMost) {
@@ -333,7 +325,6 @@ void launch_force_kernel(const ForceArgs& a, int basis, int grid, const BatchInf
                          hipStream_t st) {
   if (bi) {
     const size_t lds = sizeof(T) == 8 ? size_t(2) * a.K * sizeof(T) : 0;
-    if (lds) set_lds_limit(reinterpret_cast<const void*>(scf_force_batched_kernel<T, LBV, ACC>));
     hipLaunchKernelGGL((scf_force_batched_kernel<T, LBV, ACC>), dim3(grid), dim3(256), lds, st, a,
                        bi->offsets, bi->ustart, bi->usys, bi->nsys, bi->unit, bi->split);
   } else if constexpr (sizeof(T) == 8) {

@@ -4,10 +4,10 @@
 //
 // For each l the two radial recurrences (Gegenbauer in monic form, for the potential
 // and for d/dr) run over n, and the sums over n of recurrence value times coefficient
-// (the same coefficient for every point) come from one of two sources: the matrix cores
-// (RadialMM, FP32) or FMAs on coefficients read as uniform operands (RadialVec, FP64 and
-// Dual).  The l and m loops are compile-time, so the recurrence and derivative constants
-// are instruction literals.  The angular synthesis uses division-free identities for
+// (the same coefficient for every point) come from one of three sources: the matrix cores
+// (RadialMM, FP32 and its Dual), or FMAs on coefficients read as uniform operands
+// (RadialF64; RadialDual, FP64 with derivatives).  The l and m loops are compile-time, so
+// the recurrence and derivative constants are instruction literals.  The angular synthesis uses division-free identities for
 // dYbar/dtheta and m Ybar/sin(theta), and the result is rotated to Cartesian components.
 // The compute type may carry time derivatives (Dual), which turns the same code into the
 // jerk.
@@ -22,15 +22,7 @@
 
 namespace etics {
 
-static __constant__ BasisTables<float> g_tab32 = make_tables<float>();
 static __constant__ BasisTables<double> g_tab64 = make_tables<double>();
-
-template <typename T>
-__device__ __forceinline__ const BasisTables<T>& tab();
-template <>
-__device__ __forceinline__ const BasisTables<float>& tab<float>() { return g_tab32; }
-template <>
-__device__ __forceinline__ const BasisTables<double>& tab<double>() { return g_tab64; }
 
 // A prepared coefficient read through the constant address space (wave-uniform, so a
 // scalar load into SGPR operands); a Dual one member by member
@@ -69,12 +61,13 @@ struct ForceOut {
 // from Chat_n and W, X (d/dr) from Ehat_{n-1} (parameter a_l + 1).  Order 0 is taken in
 // closed form (Chat_0 = 1; it adds nothing to W, X since Ehat_{-1} = 0).
 //
-// RadialVec: one FMA per coefficient.  The coefficients' four arrays are read through
-// the constant address space (ConstPtr; wave-uniform scalar loads into SGPR operands) or
-// in LDS (LdsPtr); laid out [4][K], or with QUAD [K][4] (the four values of a
-// coefficient side by side, two 16-byte reads in FP64).
-template <typename T, bool ACC, int BASIS, typename P = ConstPtr<T>, bool QUAD = false>
-struct RadialVec {
+// RadialDual: FP64 with derivatives (Hernquist-Ostriker), one Dual FMA per coefficient.  The
+// coefficients' four arrays are read through the constant address space (ConstPtr;
+// wave-uniform scalar loads into SGPR operands), laid out [4][K], or in LDS (LdsPtr), with
+// QUAD [K][4] (the four values of a coefficient side by side, two 16-byte reads each).
+template <typename P, bool QUAD>
+struct RadialDual {
+  using T = Dual<double>;
   P cf;
   int K, nmax, lmax;
 
@@ -85,8 +78,6 @@ struct RadialVec {
   __device__ __forceinline__ void sums(T xi, T (&U)[l + 1], T (&V)[l + 1], T (&W)[l + 1], T (&X)[l + 1]) {
     const int WK = QUAD ? 1 : K;      // offset from one array to the next
     constexpr int IS = QUAD ? 4 : 1;  // offset from one coefficient to the next
-    using S = typename ScalarOf<T>::type;
-    const BasisTables<S>& tb = tab<S>();
     const int L2 = (lmax + 1) * (lmax + 2) / 2;
     const P cfl = cf + l * (l + 1) / 2 * IS;
 #pragma unroll
@@ -98,8 +89,8 @@ struct RadialVec {
     }
     T c2 = T(0), c1 = T(1);  // Chat_{n-2}, Chat_{n-1} for n = 1 (Chat_{-1} enters times 0)
     T e2 = T(0), e1 = T(1);  // Ehat_{n-2}, Ehat_{n-1} (parameter a_l + 1)
-    const S* ql = BASIS == kBasisCB ? tb.qcb[l] : tb.q[l];
-    const S* qdl = BASIS == kBasisCB ? tb.qdcb[l] : tb.qd[l];
+    const double* ql = g_tab64.q[l];
+    const double* qdl = g_tab64.qd[l];
     // one order per trip keeps the coefficients of a trip in registers
     for (int nn = 1; nn <= nmax; ++nn) {
       const T c = recur(xi, c1, ql[nn], c2);  // Chat_nn
@@ -111,16 +102,14 @@ struct RadialVec {
       }
       c2 = c1;
       c1 = c;
-      if constexpr (ACC) {
 #pragma unroll
-        for (int m = 0; m <= l; ++m) {
-          W[m] = fma_(e1, cload(cn + 2 * WK + m * IS), W[m]);
-          if (m > 0) X[m] = fma_(e1, cload(cn + 3 * WK + m * IS), X[m]);
-        }
-        const T e = recur(xi, e1, qdl[nn], e2);  // Ehat_nn
-        e2 = e1;
-        e1 = e;
+      for (int m = 0; m <= l; ++m) {
+        W[m] = fma_(e1, cload(cn + 2 * WK + m * IS), W[m]);
+        if (m > 0) X[m] = fma_(e1, cload(cn + 3 * WK + m * IS), X[m]);
       }
+      const T e = recur(xi, e1, qdl[nn], e2);  // Ehat_nn
+      e2 = e1;
+      e1 = e;
     }
   }
 };
@@ -141,7 +130,7 @@ struct RadialF64 {
                                        double (&X)[l + 1]) {
     const int VK = PAIR ? 1 : K;
     constexpr int IS = PAIR ? 2 : 1;
-    const BasisTables<double>& tb = tab<double>();
+    const BasisTables<double>& tb = g_tab64;
     const int L2 = (lmax + 1) * (lmax + 2) / 2;
     const P cfl = cf + l * (l + 1) / 2 * IS;
 #pragma unroll
@@ -393,7 +382,7 @@ struct RadialMM {
 };
 
 // Potential and acceleration at a point with spherical coordinates s; rad gives the radial
-// sums (RadialVec or RadialMM, whose start<0>() the caller has called)
+// sums (RadialF64, RadialDual, or RadialMM, whose start<0>() the caller has called)
 template <typename T, int LB, bool ACC, int BASIS, typename Radial>
 __device__ __forceinline__ ForceOut<T> synth_point(const Sph<T>& s, Radial& rad, int lmax) {
   using S = typename ScalarOf<T>::type;

@@ -35,17 +35,16 @@
 namespace etics {
 
 // ---------------------------------------------------------------- coefficient prep
-// FP64: prepared coefficients with their time derivatives, Dual<S> [4K] per system, the
+// FP64: prepared coefficients with their time derivatives, Dual [4K] per system, the
 // same scaling as the force pass (Hernquist-Ostriker basis); FP32: the force pass's own
 // preparation (etics_force.hip), for the matrix cores.
 //   [0,K)   (su A, su dA/dt)   [K,2K)  (su B, su dB/dt)
 //   [2K,3K) (sw A, sw dA/dt)   [3K,4K) (sw B, sw dB/dt)
-template <typename S>
 __global__ __launch_bounds__(256) void scf_jerk_prep_kernel(const double* __restrict__ A,
                                                            const double* __restrict__ B,
                                                            const double* __restrict__ Ad,
                                                            const double* __restrict__ Bd, int nmax,
-                                                           int lmax, int nsys, Dual<S>* __restrict__ cf) {
+                                                           int lmax, int nsys, Dual<double>* __restrict__ cf) {
   const int K = (nmax + 1) * (lmax + 1) * (lmax + 2) / 2;
   const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (g >= int64_t(nsys) * K) return;
@@ -60,11 +59,11 @@ __global__ __launch_bounds__(256) void scf_jerk_prep_kernel(const double* __rest
   const double s4 = -2.0 * sqrt(kPi);
   const double su = s4 * gegen_k(n, al);
   const double sw = n >= 1 ? s4 * 2.0 * al * 2.0 * gegen_k(n - 1, al + 1.0) : 0.0;
-  Dual<S>* c = cf + size_t(sys) * 4 * K;
-  c[k] = Dual<S>(S(su * A[g]), S(su * Ad[g]));
-  c[K + k] = Dual<S>(S(su * B[g]), S(su * Bd[g]));
-  c[2 * K + k] = Dual<S>(S(sw * A[g]), S(sw * Ad[g]));
-  c[3 * K + k] = Dual<S>(S(sw * B[g]), S(sw * Bd[g]));
+  Dual<double>* c = cf + size_t(sys) * 4 * K;
+  c[k] = Dual<double>(su * A[g], su * Ad[g]);
+  c[K + k] = Dual<double>(su * B[g], su * Bd[g]);
+  c[2 * K + k] = Dual<double>(sw * A[g], sw * Ad[g]);
+  c[3 * K + k] = Dual<double>(sw * B[g], sw * Bd[g]);
 }
 
 size_t jerk_prep_bytes(int nmax, int lmax, int prec) {
@@ -146,7 +145,7 @@ __device__ __forceinline__ void jerk_store(const JerkArgs& a, int64_t i, const F
 template <int LB, bool HERMITE, bool QUAD, typename CP>
 __device__ __forceinline__ void jerk_point_f64(const JerkArgs& a, CP cf, int64_t i) {
   const auto s = sph_dual<double, kBasisHO, true>(a.x[i], a.y[i], a.z[i], a.vx[i], a.vy[i], a.vz[i]);
-  RadialVec<Dual<double>, true, kBasisHO, CP, QUAD> rad{cf, a.K, a.nmax, a.lmax};
+  RadialDual<CP, QUAD> rad{cf, a.K, a.nmax, a.lmax};
   jerk_store<double, HERMITE>(a, i, synth_point<Dual<double>, LB, true, kBasisHO>(s, rad, a.lmax));
 }
 // one system's prepared coefficients, [4][K], to the workgroup's LDS as [K][4]
@@ -285,11 +284,11 @@ struct JerkBatch {
 
 template <typename S, int LBV>
 void launch_jerk_kernel(const JerkArgs& a, int grid, const JerkBatch* bi, hipStream_t st) {
-  // FP64 from LDS: 4 K Dual values (at the largest cutoffs 158 KiB; failures surface at the
-  // launch)
+  // FP64 from LDS: 4 K Dual values, at the largest cutoffs 158 KiB; more than 64 KiB has to be
+  // allowed first (failures surface at the launch)
   const size_t lds = sizeof(S) == 8 && (bi || kJerkLds<S, LBV>) ? size_t(4) * a.K * sizeof(Dual<S>) : 0;
   auto allow = [&](const void* kfn) {
-    if (lds) (void)hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (lds > 64 * 1024) (void)hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   };
   if (bi) {
     allow(reinterpret_cast<const void*>(scf_jerk_batched_kernel<S, LBV>));
@@ -334,8 +333,8 @@ int launch_jerk_prep(const double* A, const double* B, const double* Ad, const d
     return launch_force_prep_mm(A, B, Ad, Bd, nmax, lmax, nsys, kBasisHO, reinterpret_cast<float*>(cf), st);
   const int K = coeff_count(nmax, lmax);
   const int pb = int((int64_t(nsys) * K + 255) / 256);
-  hipLaunchKernelGGL(scf_jerk_prep_kernel<double>, dim3(pb), dim3(256), 0, st, A, B, Ad, Bd, nmax, lmax,
-                       nsys, reinterpret_cast<Dual<double>*>(cf));
+  hipLaunchKernelGGL(scf_jerk_prep_kernel, dim3(pb), dim3(256), 0, st, A, B, Ad, Bd, nmax, lmax, nsys,
+                     reinterpret_cast<Dual<double>*>(cf));
   return hip_fail(hipGetLastError(), "scf_jerk_prep_kernel launch");
 }
 

@@ -1298,7 +1298,7 @@ __global__ __launch_bounds__(kMexTile, LB <= 10 ? 3 : 2) void mex_force_staged_k
 // ================================================================ host side
 namespace {
 
-// the whole 160 KiB of a CU may be requested as LDS (failures surface at the launch)
+// more than 64 KiB of dynamic LDS has to be allowed first (failures surface at the launch)
 void set_lds_limit(const void* kfn) {
   (void)hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
 }
@@ -1428,7 +1428,7 @@ int launch_mex_force(const double* x, const double* y, const double* z, const do
   int rc = ETICS_OK;
   if (n <= kRankMost) {
     const size_t lds = size_t(n) * 8;
-    set_lds_limit(reinterpret_cast<const void*>(mex_rank_kernel));
+    if (lds + 1024 > 64 * 1024) set_lds_limit(reinterpret_cast<const void*>(mex_rank_kernel));  // (and its counts)
     hipLaunchKernelGGL(mex_rank_kernel, dim3(int((n + kRankTargets - 1) / kRankTargets)), dim3(kRankThreads), lds, st,
                        x, y, z, int(n), i0);
     rc = hip_fail(hipGetLastError(), "mex_rank_kernel launch");
