@@ -7,8 +7,9 @@
 // (the same coefficient for every point) come from one of three sources: the matrix cores
 // (RadialMM, FP32 and its Dual), or FMAs on coefficients read as uniform operands
 // (RadialF64; RadialDual, FP64 with derivatives).  The l and m loops are compile-time, so
-// the recurrence and derivative constants are instruction literals.  The angular synthesis uses division-free identities for
-// dYbar/dtheta and m Ybar/sin(theta), and the result is rotated to Cartesian components.
+// the recurrence and derivative constants are instruction literals.  The angular synthesis
+// uses division-free identities for dYbar/dtheta and m Ybar/sin(theta), and the result is
+// rotated to Cartesian components.
 // The compute type may carry time derivatives (Dual), which turns the same code into the
 // jerk.
 #pragma once
