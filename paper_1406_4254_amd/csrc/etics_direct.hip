@@ -7,11 +7,11 @@
 // (G = 1).  The particle itself, and any other particle at exactly the same position,
 // adds nothing.
 //
-// What bounds it is FP64 issue: about 30 issue slots a pair, of which the reciprocal
-// square root took most when it came from the math library (49 slots a pair; 12.1 ms at
-// n = 10^5, now 8.7 to 9.6 from run to run; n = 1000: 70 -> 11 us).  The sources are split
-// over the lanes and wavefronts of a workgroup, so that small n fills the chip too and
-// large n leaves no long last round:
+// What bounds it is FP64 issue: 23 instructions in about 26 issue slots a pair (0.83 of the
+// slots taken), of which the reciprocal square root took most when it came from the math
+// library (49 slots a pair; 12.1 ms at n = 10^5, now 8.7 to 9.6 from run to run; n = 1000:
+// 70 -> 11 us).  The sources are split over the lanes and wavefronts of a workgroup, so
+// that small n fills the chip too and large n leaves no long last round:
 // a workgroup holds 16 NT targets (16 lanes, NT targets a lane), its 4 WAVES slices of
 // lanes each take every (4 WAVES)-th source, and the slices are added in a fixed order.
 #include <hip/hip_runtime.h>
